@@ -22,7 +22,7 @@ struct Layout {
   size_t dev, sweep_ctr, x, y, cell_of, reg_of, cell_ids, reg_count, reg_fill, cell_start, reg_start,
       acc_delta, acc_cnt,
       ring, cell_digest, draws, err, red, chain_start, chain_dir, shuffle, dbg, psi, psi_part, psi_red,
-      gr, queue, cell_done, psi_nb, psi_err, ovl, total;
+      gr, queue, cell_done, psi_nb, psi_err, obs_pos, obs_id, obs_list, obs_count, obs_range, obs_ctr, ovl, total;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -71,6 +71,12 @@ Layout make_layout(int64_t n, int32_t C, int32_t chains_per_cell, bool sweep_onl
   l.cell_done = o;  o = align256(o + 8 * nc);
   l.psi_nb = o;     o = align256(o + 4 * no);
   l.psi_err = o;    o = align256(o + (sweep_only ? 0 : 16));
+  l.obs_pos = o;    o = align256(o + 16 * no);
+  l.obs_id = o;     o = align256(o + 4 * no);
+  l.obs_list = o;   o = align256(o + 4 * no);
+  l.obs_count = o;  o = align256(o + 4 * no);
+  l.obs_range = o;  o = align256(o + 8 * no);
+  l.obs_ctr = o;    o = align256(o + (sweep_only ? 0 : 4 * (size_t)ec::kObsCounters));
   l.ovl = o;        o = align256(o + 32);
   l.total = o;
   return l;
@@ -324,6 +330,8 @@ ec::LaunchShape shape_of(const ec::Dev& d, const ec_params& p) {
   sh.periodic = d.C == 1;
   sh.any_distinct = d.start_mode == 1;
   sh.fp32_screen = d.precision == EC_PREC_FP32_SCREEN;
+  sh.box = d.L;
+  sh.sigma = d.sigma;
   sh.max_n = d.n;
   sh.max_chains = d.chains_per_cell > 0 ? (int64_t)d.C * d.C * d.chains_per_cell : d.n;
   sh.max_cells = d.C * d.C;
@@ -397,6 +405,12 @@ void fill_record(ec::Dev* out, const ec_params* p, const Derived& dv, unsigned c
   d.cell_done = (int64_t*)(b + lay.cell_done);
   d.psi_nb = (int32_t*)(b + lay.psi_nb);
   d.psi_err = (unsigned long long*)(b + lay.psi_err);
+  d.obs_pos = (double2*)(b + lay.obs_pos);
+  d.obs_id = (int32_t*)(b + lay.obs_id);
+  d.obs_list = (int32_t*)(b + lay.obs_list);
+  d.obs_count = (int32_t*)(b + lay.obs_count);
+  d.obs_range = (int2*)(b + lay.obs_range);
+  d.obs_ctr = (int32_t*)(b + lay.obs_ctr);
   d.ovl = (unsigned long long*)(b + lay.ovl);
   d.check_overlap = (p->flags & EC_FLAG_CHECK_OVERLAP) ? 1 : 0;
   d.stripes = (p->flags & EC_FLAG_STRIPES) ? 1 : 0;
@@ -1357,6 +1371,12 @@ ec_status ec_sweep_static(const ec_params* p, double* x, double* y, int64_t firs
   d.psi_nb = nullptr;
   d.psi_err = nullptr;
   d.gr_counts = nullptr;
+  d.obs_pos = nullptr;
+  d.obs_id = nullptr;
+  d.obs_list = nullptr;
+  d.obs_count = nullptr;
+  d.obs_range = nullptr;
+  d.obs_ctr = nullptr;
   ec::Dev* dd = (ec::Dev*)(b + lay.dev);
   const ec::LaunchShape sh = shape_of(d, *p);
   const hipStream_t hs = (hipStream_t)stream;

@@ -59,6 +59,9 @@ constexpr int kMaxDrawTries = 256;
 constexpr int kDebugWords = 16;
 
 constexpr int kDigestRing = 1024;
+// Counters of the observables' grid: places of the sorted arrays taken, disks
+// on the Delaunay list.
+enum { OBS_CURSOR = 0, OBS_LISTED = 1, kObsCounters = 2 };
 // Bins of the pair histogram (pressure route).
 constexpr int kMaxGrBins = 1024;
 // Events hashed together, one per lane, by the walled-cell kernel's digest
@@ -99,6 +102,12 @@ struct Dev {
   double* psi_red;                  // [3] Psi (re, im) and the mean neighbour count
   int32_t* psi_nb;                  // [N] Delaunay neighbour count of each disk
   unsigned long long* psi_err;      // [2] disks whose Voronoi cell was not certified; candidate overflows
+  double2* obs_pos;                 // [N] observables: positions grouped by the cells of their grid
+  int32_t* obs_id;                  // [N] ids in that order
+  int32_t* obs_list;                // [N] sorted places whose Delaunay neighbours need the wide search
+  int32_t* obs_count;               // [N] disks per grid cell (never more cells than disks)
+  int2* obs_range;                  // [N] sorted range of each grid cell
+  int32_t* obs_ctr;                 // [kObsCounters]
   unsigned long long* gr_counts;    // [kMaxGrBins + 1] pair counts per bin, then pairs < sigma
   int32_t* queue;                   // [1] ticket counter of the one-launch sweep
   int64_t* cell_done;               // [C*C] last sweep + 1 whose write-back the cell has published
@@ -196,6 +205,7 @@ struct LaunchShape {
   bool reject;              // rejection at the cell boundary (same for all)
   bool check_overlap;       // some system checks for overlaps after every sweep
   bool stripes;             // striped decomposition (same for all)
+  double box, sigma;        // box side and disk diameter (observables: a system alone)
   int64_t max_n;            // disks
   int64_t max_chains;       // chains per sweep
   int32_t max_cells;        // C * C
@@ -229,18 +239,15 @@ hipError_t set_phase_lds_limit(int bytes);
 // times CUs times cells per workgroup).
 hipError_t ready_queue_workers(int lds_per_cell, int cpb, int fp32, int reject, int* workers);
 hipError_t launch_zero_tallies(const Dev* ds, int32_t n_cells, hipStream_t st);
-// Hexatic order parameter of one system (cutoff neighbours within r_cut,
-// r_cut <= cell side): rebin of the current sweep, per-disk Psi_k, and a
-// fixed-order reduction into psi_red.
-// Cell lists of the current grid (sweep draws, count, offsets, scatter), for
-// the observables of ec_observe.hip; one walled system.
-hipError_t launch_rebin(const Dev* ds, const LaunchShape& sh, hipStream_t st);
+// Hexatic order parameter of one system (cutoff neighbours within r_cut):
+// the observables' grid, per-disk Psi_k, and a fixed-order reduction into
+// psi_red.
 hipError_t launch_psi6(const Dev* ds, const LaunchShape& sh, double r_cut, hipStream_t st);
-// Add the current configuration's ordered-pair counts (bins of width delta =
-// (r_max - sigma)/n_bins from sigma; r_max <= cell side) to gr_counts.
 // Psi with Delaunay neighbours: candidates within r_search, Voronoi cells
 // certified within r_search / 2.
 hipError_t launch_psi6_delaunay(const Dev* ds, const LaunchShape& sh, double r_search, hipStream_t st);
+// Add the current configuration's ordered-pair counts (bins of width delta =
+// (r_max - sigma)/n_bins from sigma) to gr_counts.
 hipError_t launch_gr(const Dev* ds, const LaunchShape& sh, double r_max, double delta, int n_bins,
                      hipStream_t st);
 // Allocation-free sweeps (ec_sweep_static): bytes of the library's static
