@@ -93,7 +93,10 @@ __global__ void __launch_bounds__(256) k_grid_scatter(const Dev* __restrict__ ds
 }
 
 // Ranges of the 3 x 3 cells around a position (the one cell of a 1 x 1 grid,
-// and empty ranges beside it).
+// and empty ranges beside it).  The three cells of a row that lie one behind
+// the other in the sorted arrays (all but those at the box edge or at the end
+// of a workgroup's 1024 cells) become one range: three short loops fewer per
+// row, and lanes whose cells differ in size wait less for each other.
 __device__ __forceinline__ void grid_block(const Dev& d, const Grid& g, double2 p, int2 (&r)[9]) {
   const int cx = grid_axis(p.x, g), cy = grid_axis(p.y, g);
 #pragma unroll
@@ -102,6 +105,12 @@ __device__ __forceinline__ void grid_block(const Dev& d, const Grid& g, double2 
     nx += nx < 0 ? g.G : (nx >= g.G ? -g.G : 0);
     ny += ny < 0 ? g.G : (ny >= g.G ? -g.G : 0);
     r[k] = (g.G > 1 || k == 4) ? d.obs_range[ny * g.G + nx] : make_int2(0, 0);
+  }
+#pragma unroll
+  for (int k = 0; k < 9; k += 3) {
+    const bool joined = r[k].y == r[k + 1].x && r[k + 1].y == r[k + 2].x;
+    if (joined) r[k].y = r[k + 2].y;
+    if (joined) r[k + 1] = r[k + 2] = make_int2(0, 0);
   }
 }
 
@@ -139,8 +148,8 @@ __device__ __forceinline__ void store_psi(const Dev& d, int id, long long fre, l
 // found are put aside in LDS and their bond terms, two divisions each, taken
 // together afterwards: of about 16 disks tested 6 are neighbours, and each
 // lane's 6 come at other places of its scan.  Bound by instruction issue (about
-// 20 B per disk are read and written): 74 us for 1.2M disks at eta 0.72, the
-// grid before it 60 us; 6.3 ms as a scan of the simulation cells of 290 disks.
+// 20 B per disk are read and written): 71 us for 1.2M disks at eta 0.72, the
+// grid before it 55 us; 6.3 ms as a scan of the simulation cells of 290 disks.
 // ---------------------------------------------------------------------------
 constexpr int kStash = 8;
 
@@ -256,7 +265,7 @@ __global__ void __launch_bounds__(1024) k_psi6_final(const Dev* __restrict__ ds,
 // wavefront per disk, for the listed disks; a disk not certified there either,
 // or with more than kMaxCand candidates, is counted in psi_err and the host
 // reports it.  The cost of a disk grows with the square of its candidates, and
-// in a dense system few disks are listed.  Bound by instruction issue: 0.58 ms
+// in a dense system few disks are listed.  Bound by instruction issue: 0.50 ms
 // for 1.2M disks at eta 0.72, against 12.3 ms with every disk's candidates
 // within r_search, taken from the simulation cells.
 // ---------------------------------------------------------------------------
@@ -436,8 +445,8 @@ __global__ void __launch_bounds__(256) k_delaunay_far(const Dev* __restrict__ ds
 // together.  Counts go to a histogram per workgroup in LDS, then to the global
 // one (integers: exact and independent of order); the workgroups go over the
 // disks in strides, since each adds all its bins to the global counts at the
-// end.  Pairs closer than sigma are counted apart.  34 us for 303k disks in
-// random order (r_max 1.5, 500 bins), the grid before it 42 us; 12.2 ms as a
+// end.  Pairs closer than sigma are counted apart.  36 us for 303k disks in
+// random order (r_max 1.5, 500 bins), the grid before it 41 us; 12.2 ms as a
 // scan of the simulation cells.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_gr(const Dev* __restrict__ ds, Grid g, double r_max, double delta,
