@@ -192,26 +192,26 @@ class System:
         """Hexatic order parameter with cutoff neighbours: (Psi, mean neighbour
         count[, per-disk Psi_k as a complex array])."""
         re, im, nb = C.c_double(), C.c_double(), C.c_double()
-        per = np.zeros(2 * self.n, dtype=np.float64) if per_disk else None
+        per = np.empty(self.n, dtype=np.complex128) if per_disk else None
         _check(self._lib.ec_measure_psi6(self.h, float(r_cut), C.byref(re), C.byref(im), C.byref(nb),
                                          _dptr(per) if per_disk else None),
                self.h, "ec_measure_psi6")
         out = (complex(re.value, im.value), nb.value)
-        return out + (per[0::2] + 1j * per[1::2],) if per_disk else out
+        return out + (per,) if per_disk else out
 
     def measure_psi6_delaunay(self, r_search=0.0, per_disk=False):
         """Hexatic order parameter with Delaunay neighbours: (Psi, mean neighbour
         count[, per-disk Psi_k as a complex array, per-disk neighbour counts])."""
         re, im, nb = C.c_double(), C.c_double(), C.c_double()
-        per = np.zeros(2 * self.n, dtype=np.float64) if per_disk else None
-        cnt = np.zeros(self.n, dtype=np.int32) if per_disk else None
+        per = np.empty(self.n, dtype=np.complex128) if per_disk else None
+        cnt = np.empty(self.n, dtype=np.int32) if per_disk else None
         _check(self._lib.ec_measure_psi6_delaunay(
             self.h, float(r_search), C.byref(re), C.byref(im), C.byref(nb),
             _dptr(per) if per_disk else None,
             cnt.ctypes.data_as(C.POINTER(C.c_int32)) if per_disk else None),
             self.h, "ec_measure_psi6_delaunay")
         out = (complex(re.value, im.value), nb.value)
-        return out + (per[0::2] + 1j * per[1::2], cnt) if per_disk else out
+        return out + (per, cnt) if per_disk else out
 
     def gr_accumulate(self, r_max, n_bins):
         """Add the current configuration's ordered-pair counts to the histogram."""
