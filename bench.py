@@ -320,7 +320,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f64" if precision == "fp64" else "f32-screen+f64",
+        "dtype": "f64",
         "data": "synthetic",
         "config": {"workload": args.workload, "n_disks": w["n"], "eta": w["eta"],
                    "cells_per_side": w["cells"], "ell": w["ell"],
@@ -471,7 +471,7 @@ def bench_batch(args, torch, P):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f64" if precision == "fp64" else "f32-screen+f64",
+        "dtype": "f64",
         "data": "synthetic",
         "config": {"workload": "batch64", "n_systems": len(ps),
                    "sum_n": int(sum(c["n"] for c in cfgs)), "eta_range": [0.30, 0.72],

@@ -329,7 +329,6 @@ ec::LaunchShape shape_of(const ec::Dev& d, const ec_params& p) {
   sh.n_sys = 1;
   sh.periodic = d.C == 1;
   sh.any_distinct = d.start_mode == 1;
-  sh.fp32_screen = d.precision == EC_PREC_FP32_SCREEN;
   sh.box = d.L;
   sh.sigma = d.sigma;
   sh.max_n = d.n;
@@ -346,29 +345,6 @@ ec::LaunchShape shape_of(const ec::Dev& d, const ec_params& p) {
   sh.stripes = d.stripes != 0;
   if (sh.stripes) sh.one_launch = false;
   return sh;
-}
-
-// Error bounds of the FP32 screen.  With u = 2^-24, coordinates of staged
-// disks bounded by X = w + 2 sigma and window offsets by R = 9b (an 8 x 8-bin
-// window reaches at most 6 bins along each axis from the moving disk), the FP32
-// offsets are within u (2X + R) of the exact ones, so a = r.d and c = r x d
-// are within Ea = u (4X + 8R) (also covering the FP64 values), sigma^2 - c^2
-// within Ed = 2 (sigma + Ea) Ea + 4 u sigma^2, and where the FP32
-// sigma^2 - c^2 exceeds Dg = sigma^2 / 64 its square root is within
-// Ed / sqrt(Dg - Ed) + 2 u sigma.  Each bound is doubled; the caller's
-// relative margin (times sigma) is added to the distance bound.
-void screen_bounds(ec::Dev* d) {
-  const double u = std::ldexp(1.0, -24);
-  const double sg = d->sigma, X = d->w + 2.0 * sg, R = 9.0 * d->b;
-  const double ea = 2.0 * u * (4.0 * X + 8.0 * R);
-  const double ed = 2.0 * (2.0 * (sg + ea) * ea + 4.0 * u * sg * sg);
-  const double dg = sg * sg / 64.0;
-  const double es = 2.0 * (ed / std::sqrt(dg - ed) + 2.0 * u * sg);
-  const double e = ea + es + 4.0 * u * (R + sg) + d->margin * sg;
-  d->scr_ea = (float)ea;
-  d->scr_ed = (float)ed;
-  d->scr_dg = (float)dg;
-  d->scr_e = (float)e;
 }
 
 // The device record of a system whose workspace region starts at b.
@@ -430,7 +406,7 @@ void fill_record(ec::Dev* out, const ec_params* p, const Derived& dv, unsigned c
   d.cap = 0.5 * dv.L - p->sigma;
   d.C = p->cells_per_side;
   d.nb = dv.nb;
-  d.gridb = dv.nb + 4;  // own bins 2..nb+1, two rings of frozen-band bins around them
+  d.gridb = dv.nb + 4;  // nb own bins, two rings of frozen-band bins around them
   d.pbins = dv.pbins;
   d.b = dv.nb > 0 ? dv.w / (double)dv.nb : 0.0;
   d.inv_b = dv.nb > 0 ? 1.0 / d.b : 0.0;
@@ -438,13 +414,10 @@ void fill_record(ec::Dev* out, const ec_params* p, const Derived& dv, unsigned c
   // which two cells' local coordinates of one disk can disagree (w >= 3 sigma
   // keeps the strips apart)
   d.strip = p->sigma + 1e-9 * dv.L;
-  d.margin = p->screen_margin > 0.0 ? p->screen_margin : 1e-5;  // relative to sigma
   d.cap_own = dv.cap_own;
   d.chains_per_cell = p->chains_per_cell;
   d.dir_mode = p->dir_mode;
   d.start_mode = p->start_mode;
-  d.precision = p->precision;
-  if (p->precision == EC_PREC_FP32_SCREEN) screen_bounds(&d);
   d.lds_per_cell = dv.lds_per_cell;
   d.cells_per_block = dv.cpb;
   d.seed = p->seed;
@@ -1074,7 +1047,7 @@ ec_status batch_apply_schedule(ec_batch b) {
   sh.ready_queue = b->schedule == EC_SCHEDULE_READY_QUEUE && !sh.stripes;
   if (sh.ready_queue) {
     int workers = 0;
-    hipError_t e = ec::ready_queue_workers(sh.max_lds_per_cell, sh.cpb, sh.fp32_screen ? 1 : 0,
+    hipError_t e = ec::ready_queue_workers(sh.max_lds_per_cell, sh.cpb,
                                            sh.reject ? 1 : 0, &workers);
     if (e != hipSuccess) {
       b->last_error = std::string("ready-queue occupancy: ") + hipGetErrorString(e);
@@ -1190,7 +1163,6 @@ ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* ws, size_t ws_
   std::memset(&sh, 0, sizeof sh);
   sh.n_sys = n_sys;
   sh.periodic = false;
-  sh.fp32_screen = ps[0].precision == EC_PREC_FP32_SCREEN;
   sh.reject = (ps[0].flags & EC_FLAG_REJECT) != 0;
   sh.stripes = (ps[0].flags & EC_FLAG_STRIPES) != 0;
   sh.cpb = 1;

@@ -114,16 +114,12 @@ struct Dev {
   unsigned long long* ovl;          // [4] overlap check: pairs found, first pair (i, j), its sweep
 
   int64_t n;
-  double sigma, sig2, ell, L, half_L, w, cap, b, inv_b, margin;
+  double sigma, sig2, ell, L, half_L, w, cap, b, inv_b;
   // width of the wall strips that split a cell into 3 x 3 regions: sigma plus
   // a margin far above the rounding of cell-local coordinates, so every disk a
   // neighbour stages as frozen lies in the strips that face it
   double strip;
-  // FP32 screen (precision 1): error bounds of the FP32 contact terms against
-  // the FP64 ones (a, sigma^2 - c^2, distance) and the threshold of
-  // sigma^2 - c^2 above which the FP32 distance is within scr_e
-  float scr_ea, scr_ed, scr_dg, scr_e;
-  int32_t C, nb, gridb, cap_own, chains_per_cell, dir_mode, start_mode, precision;
+  int32_t C, nb, gridb, cap_own, chains_per_cell, dir_mode, start_mode;
   int32_t pbins;  // one periodic cell: bins per side of its bin grid, 0 = brute-force search
   int32_t lds_per_cell, cells_per_block;
   int32_t search;                   // 0: 8x8-bin window with guard; 1: scan of every slot
@@ -138,9 +134,12 @@ struct Dev {
 
 // LDS layout of one simulation cell in the walled-cell kernel: a grid of
 // gridb x gridb square bins of side b < sigma/sqrt(2), one slot each (FP64
-// position, 32-bit meta word: own index, or frozen id | top bit); the cell's
-// id-ordered list and the slot of each own disk; one sink slot per lane (a
-// target for the lanes that do not store when one or two lanes write).
+// position, 32-bit meta word: own index, or frozen id | top bit), with
+// kSlotPad empty slots before the first and after the last (a window's columns
+// are not clamped to the grid); the cell's id-ordered list and the 16-bit slot
+// of each own disk (at most 100^2 slots); one sink slot per lane (a target for
+// the lanes that do not store when one lane writes).
+constexpr int kSlotPad = 3;
 struct CellLds {
   int32_t off_pos, off_meta, off_own_gid, off_own_loc, off_sink, off_undo, bytes;
 };
@@ -148,13 +147,13 @@ struct CellLds {
 // reject: an undo log of kUndoCap entries (slots and old position, 32 B each).
 __host__ __device__ inline CellLds cell_lds_layout(int gridb, int cap_own, bool reject) {
   CellLds l;
-  int slots = gridb * gridb;
+  int slots = gridb * gridb + 2 * kSlotPad;
   int o = 0;
   l.off_pos = o;      o += 16 * slots;
   l.off_meta = o;     o += 4 * slots;
   o = (o + 15) & ~15;
   l.off_own_gid = o;  o += 4 * cap_own;
-  l.off_own_loc = o;  o += 4 * cap_own;
+  l.off_own_loc = o;  o += 2 * cap_own;
   o = (o + 15) & ~15;
   l.off_sink = o;     o += 16 * 64;
   l.off_undo = o;     o += reject ? 32 * kUndoCap : 0;
@@ -198,7 +197,6 @@ struct LaunchShape {
   int32_t n_sys;
   bool periodic;            // one periodic cell (single system only)
   bool any_distinct;        // some system uses the distinct-start control
-  bool fp32_screen;         // the FP32-screened phase kernel (same for all)
   bool one_launch;          // all four phases in one launch (k_sweep_cells), else one per phase
   bool ready_queue;         // a batch: every cell of every system in one launch fed by a ready queue
   ReadyQueue queue;         // (ready_queue only)
@@ -237,7 +235,7 @@ hipError_t set_phase_lds_limit(int bytes);
 // Wavefronts of the ready-queue launch that fit on the device at once with
 // this much LDS per cell and cells per workgroup (resident workgroups per CU
 // times CUs times cells per workgroup).
-hipError_t ready_queue_workers(int lds_per_cell, int cpb, int fp32, int reject, int* workers);
+hipError_t ready_queue_workers(int lds_per_cell, int cpb, int reject, int* workers);
 hipError_t launch_zero_tallies(const Dev* ds, int32_t n_cells, hipStream_t st);
 // Hexatic order parameter of one system (cutoff neighbours within r_cut):
 // the observables' grid, per-disk Psi_k, and a fixed-order reduction into

@@ -9,7 +9,7 @@
 // cell's own disks and its frozen neighbours (centres within sigma outside
 // the cell) are staged in LDS in a grid of square bins of side b <
 // sigma/sqrt(2); such a bin holds at most one centre of a configuration
-// without overlaps, so one slot per bin suffices and a cell takes about 20 KB
+// without overlaps, so one slot per bin suffices and a cell takes about 19 KB
 // (eight cells, two wavefronts per SIMD, per CU).  One event search reads an
 // 8 x 8 window of bins around the moving disk, one slot per lane, computes
 // the contact distance of every slot in FP64, and takes a wave-wide minimum
@@ -140,10 +140,10 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
   v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));
   v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));
   v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));
-  // rows outside a broadcast's mask may take any value: only rows 1 and 3
-  // (then row 3) are read afterwards
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x142, 0xA, 0xF, false));
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x143, 0xC, 0xF, false));
+  // (rows outside a broadcast's mask take the identity, so that each step is
+  // one instruction; only rows 1 and 3, then row 3, are read afterwards)
+  v = umin_(v, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
+  v = umin_(v, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
@@ -198,20 +198,6 @@ __device__ __forceinline__ int wave_argmin(double s, uint32_t id, bool valid) {
     }
   }
   return wl;
-}
-
-// Minimum of a 32-bit value over the 64 lanes, left in every lane: DPP steps
-// within rows of 16, then the gfx950 row-pair and half-wave swaps (no trip
-// through a scalar register).
-__device__ __forceinline__ unsigned wave_min_all(unsigned v) {
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));
-  v = umin_(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));
-  const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = umin_((unsigned)r16[0], (unsigned)r16[1]);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return umin_((unsigned)r32[0], (unsigned)r32[1]);
 }
 
 // As wave_argmin, with the minimum of the high words kept in every lane.
@@ -743,14 +729,46 @@ __device__ __forceinline__ int32_t load_err(const Dev& d) {
   return __hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// PREC 0: FP64 contact distances; PREC 1: FP32 screen, FP64 for the survivors.
+// Both components of (x, y) / den: the compiler's own FP64 division sequence
+// (reciprocal estimate, two Newton steps, quotient, one correction with the
+// exact residual), with the reciprocal formed once and without the range
+// scaling and special-value fix-up, which do nothing for a denominator between
+// 2^-300 and 2^301 and numerators that are 0 or above 2^-960: the same
+// quotients.
+__device__ __forceinline__ void div_pair(double x, double y, double den, double& qx, double& qy) {
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(r, fma(-den, r, 1.0), r);
+  r = fma(r, fma(-den, r, 1.0), r);
+  qx = x * r;
+  qx = fma(fma(-den, qx, x), r, qx);
+  qy = y * r;
+  qy = fma(fma(-den, qy, y), r, qy);
+}
+
+__device__ __forceinline__ int hi_word(double v) {
+  return (int)((uint64_t)__double_as_longlong(v) >> 32);
+}
+
 // One active cell of colour phase q (Sec. 3.4, steps 3-6): stage the own
 // disks and the frozen band into LDS, run the cell's chains, write back.  One
 // wavefront; base is its LDS region.  Returns early, with d.err set, when a
 // capacity check fails.  REJ 1: a chain that reaches a wall or a frozen disk
-// is rejected and undone (the rejection variant of Sec. 3.4); every event then
-// takes the general path, which logs each lift for the undo.
-template <int PREC, int REJ>
+// is rejected and undone (the rejection variant of Sec. 3.4); each lift is
+// logged for the undo.
+//
+// What bounds it: a cell's events are one serial chain, and a wavefront alone
+// on its SIMD issues one instruction per 4 to 5 cycles whatever its kind.  Four
+// things cost more: a scalar instruction that reads what a vector one has just
+// written (about 15 cycles of waiting), a branch (10 cycles not taken, 25
+// taken), the FP64 reciprocal square root (16) and the LDS round trip (60 for
+// the reads, 90 behind a store).  So the plain event below makes its tests in
+// vector registers as sign bits that are ANDed into one word, reads that word
+// once; everything the next window's address does not need stands behind the
+// read.  Measured: 1M disks (one wavefront per SIMD) 122.9 -> 100.6 ms a sweep
+// against tests made by compares joined in scalar registers, with the whole
+// window clamped and the moved centre recomputed from the winner's distance;
+// 16 x 16 cells of 64 disks 16.8 -> 13.4 ms.
+template <int REJ>
 __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, const SweepDraws& dr,
                                            const int q, const int blk, unsigned char* const base,
                                            const int lane) {
@@ -763,27 +781,27 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   const double L = d.L, half_L = d.half_L, w = d.w, sigma = d.sigma, sig2 = d.sig2;
   const int gridb = d.gridb, nb = d.nb;
   const int nslots = gridb * gridb;  // one slot per bin
-  // bin coordinates of a slot: by = floor(slot / gridb) as (slot * m) >> 20
-  // with m = ceil(2^20 / gridb), exact for slot < gridb^2 when gridb^3 < 2^20
-  // (the host limits gridb to 100)
+  // Slots are counted from that of the first own bin (bin (0, 0) of nb x nb;
+  // the frozen band's bins are -2, -1, nb and nb + 1): slot = by * gridb + bx.
+  const int qoff = 2 * gridb + 2;
+  // row of an own slot: floor(slot / gridb) as (slot * m) >> 20 with m =
+  // ceil(2^20 / gridb), exact for 0 <= slot < gridb^2 when gridb^3 < 2^20 (the
+  // host limits gridb to 100)
   const uint32_t inv_g20 = ((1u << 20) + (uint32_t)gridb - 1u) / (uint32_t)gridb;
-  auto slot_bin = [&](int slot, int& bx, int& by) __attribute__((always_inline)) {
-    by = (int)(((uint32_t)slot * inv_g20) >> 20);
-    bx = slot - by * gridb;
-  };
 
   const CellLds lay = cell_lds_layout(gridb, d.cap_own, REJ == 1);
-  double2* pos = (double2*)(base + lay.off_pos);
-  uint32_t* meta = (uint32_t*)(base + lay.off_meta);
+  double2* const pos_all = (double2*)(base + lay.off_pos);
+  uint32_t* const meta_all = (uint32_t*)(base + lay.off_meta);
+  double2* const pos = pos_all + kSlotPad + qoff;
+  uint32_t* const meta = meta_all + kSlotPad + qoff;
   int32_t* own_gid = (int32_t*)(base + lay.off_own_gid);
-  int32_t* own_loc = (int32_t*)(base + lay.off_own_loc);
+  uint16_t* own_loc = (uint16_t*)(base + lay.off_own_loc);
   // the id staging buffer of the rank sort lies in the position slots, which
   // are filled only after the sort
   int32_t* tmp = (int32_t*)(base + lay.off_pos);
   // per-lane sink slots: lanes that have nothing to store write here, so a
-  // store by one or two lanes needs no change of the execution mask
+  // store by one lane needs no change of the execution mask
   double2* const sink = (double2*)(base + lay.off_sink) + lane;
-  uint32_t* const sink32 = (uint32_t*)sink;
   // REJ 1 only: per logged lift the old position, then (slot before, slot after)
   double2* undo_pos = (double2*)(base + lay.off_undo);
   int2* undo_slot = (int2*)(undo_pos + kUndoCap);
@@ -805,29 +823,29 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   }
   wave_sync();
   const double2 nan2 = make_double2(__builtin_nan(""), __builtin_nan(""));
-  for (int s = lane; s < nslots; s += 64) {
-    pos[s] = nan2;
-    meta[s] = kEmptySlot;
+  for (int s = lane; s < nslots + 2 * kSlotPad; s += 64) {
+    pos_all[s] = nan2;
+    meta_all[s] = kEmptySlot;
   }
   wave_sync();
 
-  // own disks into bins 2..nb+1: a bin's diagonal is below sigma, so it holds
+  // own disks into bins 0..nb-1: a bin's diagonal is below sigma, so it holds
   // at most one centre of a configuration without overlaps (a second one is
   // reported as a capacity error)
   for (int k = lane; k < n_own; k += 64) {
     int g = own_gid[k];
     double vx = local_coord(d.x[g], dr.sx, ox, L, half_L);
     double vy = local_coord(d.y[g], dr.sy, oy, L, half_L);
-    int bx = (int)floor(vx * d.inv_b) + 2, by = (int)floor(vy * d.inv_b) + 2;
-    bx = bx < 2 ? 2 : (bx > nb + 1 ? nb + 1 : bx);
-    by = by < 2 ? 2 : (by > nb + 1 ? nb + 1 : by);
+    int bx = (int)floor(vx * d.inv_b), by = (int)floor(vy * d.inv_b);
+    bx = bx < 0 ? 0 : (bx > nb - 1 ? nb - 1 : bx);
+    by = by < 0 ? 0 : (by > nb - 1 ? nb - 1 : by);
     const int s = by * gridb + bx;
     if (atomicCAS(&meta[s], kEmptySlot, (uint32_t)k) != kEmptySlot) {
       atomicOr(d.err, ERR_BIN_CAP);
       continue;
     }
     pos[s] = make_double2(vx, vy);
-    own_loc[k] = s;
+    own_loc[k] = (uint16_t)s;
   }
   // frozen disks: centres of the 8 neighbouring cells within sigma of this
   // cell, in the two outer rings of bins.  Only a neighbour's regions that
@@ -858,9 +876,9 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       double vx = local_coord(d.x[g], dr.sx, ox, L, half_L);
       double vy = local_coord(d.y[g], dr.sy, oy, L, half_L);
       if (vx >= -sigma && vx <= w + sigma && vy >= -sigma && vy <= w + sigma) {
-        int bx = (int)floor(vx * d.inv_b) + 2, by = (int)floor(vy * d.inv_b) + 2;
-        bx = bx < 0 ? 0 : (bx > nb + 3 ? nb + 3 : bx);
-        by = by < 0 ? 0 : (by > nb + 3 ? nb + 3 : by);
+        int bx = (int)floor(vx * d.inv_b), by = (int)floor(vy * d.inv_b);
+        bx = bx < -2 ? -2 : (bx > nb + 1 ? nb + 1 : bx);
+        by = by < -2 ? -2 : (by > nb + 1 ? nb + 1 : by);
         const int s = by * gridb + bx;
         if (atomicCAS(&meta[s], kEmptySlot, (uint32_t)g | kFrozenBit) != kEmptySlot) {
           atomicOr(d.err, ERR_BIN_CAP);
@@ -885,20 +903,23 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   uint32_t rec_lo = 0, rec_hi = 0, rec_tag = 0;
   // lane = lx + 8 ly: one bin of an 8 x 8 window per lane, a window row in 8
   // neighbouring lanes
-  const int lx = lane & 7, ly = lane >> 3;
-  const int loff = ly * gridb + lx;  // this lane's slot inside a window
+  const int loff = (lane >> 3) * gridb + (lane & 7);  // this lane's slot inside a window
   const double inv_b = d.inv_b;
   // A window of 8 x 8 bins reaches 2 bins behind the moving disk's bin and 5
-  // ahead of it along each axis (clamped windows only add room, since nothing
-  // is staged beyond the outer bins).  With sigma/2 < b < sigma/sqrt(2), the
-  // 2b behind cover sigma, and a move of length t keeps its
-  // sigma-neighbourhood inside the window whenever t * max(|dx|, |dy|) <=
-  // 5b - sigma - eps: then no disk outside the window can be hit first, and
-  // the event found in the window is exact.
+  // ahead of it along each axis.  With sigma/2 < b < sigma/sqrt(2), the 2b
+  // behind cover sigma, and a move of length t keeps its sigma-neighbourhood
+  // inside the window whenever t * max(|dx|, |dy|) <= 5b - sigma - eps: then no
+  // disk outside the window can be hit first, and the event found in the window
+  // is exact.  Rows are clamped to the grid (nothing is staged beyond it).
+  // Columns are not: a window across the left or right edge reads the end of
+  // the row before or the start of the row after, which are slots of the same
+  // cell (or, before the first and after the last slot, kSlotPad empty ones);
+  // more disks tested change no minimum.
   const double eps = 1e-9 * sigma;
   const double reach = 5.0 * d.b - sigma - eps;
-  // a plain lift keeps the moved centre in [wlo, whi] on both axes (see there)
-  const double wlo = eps, whi = w - eps;
+  // a plain lift keeps the moved centre in [eps, w - eps] on both axes, that is
+  // |v - mid| < inner (see there)
+  const double mid = 0.5 * w, inner = 0.5 * w - eps;
   const bool use_window = d.search == 0;
   const uint64_t wall_x_id = (uint64_t)d.n, wall_y_id = (uint64_t)d.n + 1, end_id = (uint64_t)d.n + 3;
   int aborted = 0;
@@ -912,48 +933,43 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   for (int64_t k = 0; k < n_m && aborted == 0; ++k) {
     int j = uniform_i32(nxt_start);
     if (j < 0 || j >= n_own) j = 0;  // guarded: the draw kernel writes indices below n_own
-    const double2 dir = nxt_dir;
-    double dx = dir.x, dy = dir.y;
+    double dx = nxt_dir.x, dy = nxt_dir.y;
     stop = uniform_i32(nxt_err);
     if (k + 1 < n_m) {
       nxt_start = d.chain_start[cbase + k + 1];
       nxt_dir = d.chain_dir[cbase + k + 1];
     }
     nxt_err = load_err(d);
-    // per-direction constants
-    double idx, idy, wallx, wally, idxw, idyw, dsafe;
-    int xneg, yneg;
+    // per direction: the window's origin relative to the mover's bin, and the
+    // longest move it vouches for, reach / max(|dx|, |dy|) from the hardware's
+    // reciprocal (good to about 2^-24), made smaller by 2^-20: only ever a guard
+    double dsafe;
+    int offx, offy;
 #define EC_SET_DIRECTION()                                                          \
     do {                                                                            \
-      idx = (dx != 0.0) ? 1.0 / dx : 0.0;                                           \
-      idy = (dy != 0.0) ? 1.0 / dy : 0.0;                                           \
-      wallx = (dx > 0.0) ? w : ((dx < 0.0) ? 0.0 : INFINITY);                       \
-      wally = (dy > 0.0) ? w : ((dy < 0.0) ? 0.0 : INFINITY);                       \
-      idxw = (dx != 0.0) ? idx : 1.0;                                               \
-      idyw = (dy != 0.0) ? idy : 1.0;                                               \
-      /* reach / max(|dx|, |dy|) as reach * min(|1/dx|, |1/dy|) (a 0 component    */ \
-      /* has a factor 1, and then the other is +-1); a few ulps off, far below     */ \
-      /* the eps the reach keeps in hand, and only ever a guard                     */ \
-      dsafe = use_window ? reach * fmin(fabs(idxw), fabs(idyw)) : -1.0;             \
-      xneg = uniform_i32(dx < 0.0 ? 1 : 0);                                         \
-      yneg = uniform_i32(dy < 0.0 ? 1 : 0);                                         \
+      const double lead_ = fmax(fabs(dx), fabs(dy));                                \
+      dsafe = use_window ? (reach * (1.0 - 0x1p-20)) * __builtin_amdgcn_rcp(lead_) : -1.0; \
+      offx = uniform_i32(dx < 0.0 ? -5 : -2);                                       \
+      offy = uniform_i32(dy < 0.0 ? -5 : -2);                                       \
     } while (0)
-    // origin bin of the 8 x 8-bin window around bin (bx, by): two bins behind
-    // the disk and five ahead of it along each axis, clamped to the grid
-#define EC_WINDOW(bx, by, xn, yn)                                                   \
+    // the 8 x 8 window of the mover in slot a_slot: this lane's slot, its
+    // position and meta word, and the mover's position
+#define EC_WINDOW()                                                                 \
     do {                                                                            \
-      wx0 = (bx) - 2 - 3 * (xn);                                                    \
-      wy0 = (by) - 2 - 3 * (yn);                                                    \
-      wx0 = max(min(wx0, gridb - 8), 0);                                            \
-      wy0 = max(min(wy0, gridb - 8), 0);                                            \
-      wbase = wy0 * gridb + wx0;                                                    \
+      const int by_ = (int)(((uint32_t)a_slot * inv_g20) >> 20);                    \
+      const int wy_ = max(min(by_ + offy, nb - 6), -2);                             \
+      widx = (a_slot + offx + (wy_ - by_) * gridb) + loff;                          \
+      p = pos[widx];                                                                \
+      m = meta[widx];                                                               \
+      const double2 ap_ = pos[a_slot];                                              \
+      ax = ap_.x;                                                                   \
+      ay = ap_.y;                                                                   \
     } while (0)
     EC_SET_DIRECTION();
-    int a_loc = uniform_i32(own_loc[j]);
+    int a_slot = uniform_i32((int)own_loc[j]);
     int a_lidx = j;
-    const double2 ap = pos[a_loc];
-    double ax = ap.x, ay = ap.y;
-    double rem = d.ell;
+    double ax, ay;
+    double nrem = -d.ell;  // minus the chain length left
     // event cap and abort polling, both at the digest flush (every 64 events
     // of the cell): the error word loaded at the previous flush (or chain
     // start) is read, the next load is issued, and the chain's event count,
@@ -967,265 +983,223 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       nxt_err = load_err(d);                                                        \
       capped = (ring_first - ev0 >= (uint64_t)kMaxEventsPerChain) ? 1 : 0;          \
     } while (0)
+#define EC_FLUSH()                                                                  \
+    do {                                                                            \
+      h ^= digest_batch(rec_lo, rec_hi, rec_tag, lane, kDigestBatch, ring_first, own_gid); \
+      if (REJ == 0) n_lift += count_lifts(rec_tag, lane, kDigestBatch);             \
+      ring_first += kDigestBatch;                                                   \
+      n_ring = 0;                                                                   \
+      EC_POLL();                                                                    \
+    } while (0)
     // REJ 1: the chain's undo log, contact sum and lifts (counted once accepted)
     int n_undo = 0;
     double chain_acc = 0.0;
     uint32_t chain_lifts = 0;
-    int wx0, wy0, wbase;
-    {
-      int bx0, by0;
-      slot_bin(a_loc, bx0, by0);
-      EC_WINDOW(bx0, by0, xneg, yneg);
-    }
-    int widx = wbase + loff;  // this lane's slot in the window
-    double2 p = pos[widx];
-    uint32_t m = meta[widx];
+    int widx;
+    double2 p;
+    uint32_t m;
+    EC_WINDOW();
     int ended = 0;  // the chain length is used up
 
     while (ended == 0 && stop == 0 && capped == 0) {
-      // the event found, and the decision (also read by the general path)
-      double tx, ty, best_s, wpx, wpy, e, step, nax, nay;
-      uint32_t wm;  // meta word of the nearest disk: own index, or id | frozen bit
-      int w_bx, w_by, w_slot, packed;
-      // (a disk can be hit exactly when best_s is finite)
-      // Plain lifts run in this inner loop, where the direction and its
-      // derived constants do not change: the general path, which can change
-      // them, sits outside it, so the common event needs no register copies
-      // where the two paths would otherwise join.  The loop leaves as soon as
-      // an event is not a plain lift, or after a poll that stops the chain.
-      // distances to the walls of the cell ahead: (wall - v) / d with 1/d
-      // precomputed, clamped at 0
-#define EC_WALLS()                                                                  \
-      do {                                                                          \
-        tx = (wallx - ax) * idxw;                                                   \
-        tx = (tx < 0.0) ? 0.0 : tx;                                                 \
-        ty = (wally - ay) * idyw;                                                   \
-        ty = (ty < 0.0) ? 0.0 : ty;                                                 \
-      } while (0)
-      // One plain-lift event; false on any other event (left to the general
-      // path) and after a poll that stops the chain.  The loop runs two per
-      // pass, so that the common event takes a taken branch only every other
-      // time; every return is a constant, so each exit is a plain branch.
+      // contact distance of the disk in this lane's window slot, its high word
+      // (all ones: no contact) and the wave minimum of those
+      double s;
+      unsigned key, key_min;
+      // One plain lift: the nearest disk in the window is not frozen and is hit
+      // within the remaining length, the window vouches for the move, and the
+      // moved centre stays inside the cell by eps on both axes, so neither wall
+      // comes first (with the wall distance (wall - v) / d rounded as the full
+      // decision rounds it, a centre that stops eps short of the wall leaves
+      // the wall farther by far more than the rounding); the centre may change
+      // bin.  This is exactly the full decision finding such a lift; every
+      // other event, and two disks whose distances agree to their high words,
+      // are left to the general path with nothing changed (false), as is the
+      // way out after a poll that stops the chain.  Every lane tests its own
+      // disk, with the winner's own values, between the steps of the wave
+      // minimum, whose results must wait two issue slots each.  The loop runs
+      // two per pass, so that the common event takes a taken branch only every
+      // other time; every return is a constant, so each exit is a plain branch.
       auto plain_event = [&]() __attribute__((always_inline)) -> bool {
-
-      // -- contact distance of the disk in this lane's window slot
-      double s = 0.0;
-      bool valid;
-      if (PREC == 0) {
-        valid = contact(p.x - ax, p.y - ay, dx, dy, sig2, s);
-      } else {
-        // FP32 screen: lanes whose FP32 terms prove the FP64 test fails drop
-        // out; lanes whose FP32 distance is certain to within scr_e of the
-        // FP64 one drop out when they cannot be the minimum; the rest (the
-        // survivors) get the FP64 distance.  The minimum over the survivors
-        // is then the FP64 minimum over the window.
-        // the FP32 coordinates are those of the FP64 slot position, rounded
-        const float rx = (float)p.x - (float)ax, ry = (float)p.y - (float)ay;
-        const float dx32 = (float)dx, dy32 = (float)dy;
-        const float a32 = fmaf(rx, dx32, ry * dy32);
-        const float c32 = fmaf(rx, dy32, -(ry * dx32));
-        const float disc32 = fmaf(-c32, c32, (float)sig2);
-        const bool maybe = a32 > -d.scr_ea && disc32 > -d.scr_ed;
-        const bool sure = a32 > d.scr_ea && disc32 > d.scr_dg;
-        const float s32 = fmaxf(a32 - __builtin_amdgcn_sqrtf(disc32), 0.0f);
-        const float hi = sure ? s32 + d.scr_e : INFINITY;
-        const float bound = __uint_as_float(wave_min_all(__float_as_uint(hi)));
-        const bool survivor = maybe && (!sure || s32 - d.scr_e <= bound);
-        valid = false;
-        if (survivor) valid = contact(p.x - ax, p.y - ay, dx, dy, sig2, s);
-      }
-      // The plain-lift test (the conditions are listed where its result is
-      // read) made by every lane on its own candidate while the wave minimum
-      // forms, so that it fills the DPP hazard slots; only the winning lane's
-      // result is used, computed with the winner's own values.  The lane also
-      // forms the slot of the moved centre's bin.
-      int plain_l, nslot_l;
-      {
+        const double rx = p.x - ax, ry = p.y - ay;
+        const double ca = fma(rx, dx, ry * dy);
+        const double cc = fma(rx, dy, -(ry * dx));
+        const double disc = fma(-cc, cc, sig2);
+        // (a root of a negative number or of an empty slot's NaN is NaN, and
+        // such a lane no candidate; the larger of NaN and 0 is 0)
+        s = fmax(ca - sqrt_contact(disc), 0.0);
+        key = fmin(ca, disc) > 0.0 ? (unsigned)hi_word(s) : 0xFFFFFFFFu;
         const double nxl = fma(s, dx, ax), nyl = fma(s, dy, ay);
-        const int bxl = (int)(nxl * inv_b) + 2, byl = (int)(nyl * inv_b) + 2;
-        plain_l = (int)((m & kFrozenBit) == 0) & (int)(s < rem) & (int)(s <= dsafe) &
-                  (int)(nxl >= wlo) & (int)(nxl <= whi) & (int)(nyl >= wlo) & (int)(nyl <= whi);
-        nslot_l = byl * gridb + bxl;
-        asm volatile("" : : "v"(plain_l));  // keep it here, beside the wave minimum
-      }
-      const unsigned key = argmin_key(s, valid);
-      const unsigned key_min = wave_min_u32(key);
-      if (__builtin_expect(key_min == 0xFFFFFFFFu, 0)) {
-        // no disk in the window: the general path decides (a wall, the chain
-        // end, or, where the window cannot vouch, a search of every slot);
-        // the nearest disk's other values are read there only for a disk
-        best_s = INFINITY;
-        wm = kFrozenBit;
-        return false;
-      }
-      {
-      // the nearest disk
-      const int wls = argmin_lane_slots(s, m, own_gid, key, key_min);
-      best_s = readlane_f64(s, wls);
-      wm = (uint32_t)readlane_i32((int)m, wls);
-      wpx = readlane_f64(p.x, wls);
-      wpy = readlane_f64(p.y, wls);
-      w_bx = wx0 + (wls & 7);
-      w_by = wy0 + (wls >> 3);
-      w_slot = readlane_i32(widx, wls);
-
-      // the decision, made in vector registers and moved to the scalar unit once
-#define EC_DECIDE(CHECK_WINDOW)                                                     \
-      do {                                                                          \
-        int kd = (best_s < INFINITY) ? ((wm & kFrozenBit) ? EV_FROZEN : EV_LIFT) : 0; \
-        e = best_s;                                                                 \
-        if (tx < e) { e = tx; kd = EV_WALL_X; }                                     \
-        if (ty < e) { e = ty; kd = EV_WALL_Y; }                                     \
-        const bool en = !(e < rem);                                                 \
-        step = en ? rem : e;                                                        \
-        nax = fma(step, dx, ax);                                                    \
-        nay = fma(step, dy, ay);                                                    \
-        /* bin of the moved centre, unclamped: a centre lies in [0, w], where    */ \
-        /* truncation gives bins 2..nb+1, and nb + 2 only on the far wall (or    */ \
-        /* one rounding past it); that case counts as a bin change and the      */ \
-        /* general path clamps it                                               */ \
-        const int bx_ = (int)(nax * inv_b) + 2;                                     \
-        const int by_ = (int)(nay * inv_b) + 2;                                     \
-        bool ok_ = true;                                                            \
-        if (CHECK_WINDOW) ok_ = step <= dsafe;                                      \
-        const int cr_ = (bx_ != abx || by_ != aby) ? 1 : 0;                          \
-        packed = uniform_i32(bx_ | (by_ << 8) | (kd << 16) | ((en ? 1 : 0) << 20) | \
-                             ((ok_ ? 1 : 0) << 21) | (cr_ << 22));                  \
-      } while (0)
-      // The common event, a plain lift: the nearest disk (not frozen) is hit
-      // within the remaining chain length, the window vouches for the move,
-      // and the moved centre stays inside the cell by the margin wmargin on
-      // both axes, so neither wall comes first (with the wall distance
-      // (wall - v) / d rounded as the full decision rounds it, a centre that
-      // stops wmargin short of the wall leaves the wall farther by far more
-      // than the rounding); the centre may change bin.  This is exactly the
-      // full decision (EC_DECIDE) finding such a lift; the general path makes
-      // the full decision for every other event.
-      nax = fma(best_s, dx, ax);
-      nay = fma(best_s, dy, ay);
-      const int nslot = readlane_i32(nslot_l, wls);
-      // any other event goes to the general path
-      if (__builtin_expect(REJ == 1 || readlane_i32(plain_l, wls) == 0, 0)) return false;
-      {
+        const double left = s + nrem;  // minus the length left after this lift
+        const double wall = fmax(fabs(nxl - mid), fabs(nyl - mid)) - inner;
+        const int nslot = (int)(nyl * inv_b) * gridb + (int)(nxl * inv_b);
+        // sign bit: plain; below it the slot of the moved centre
+        const int code = (int)(((unsigned)(hi_word(left) & hi_word(s - dsafe) & hi_word(wall)) & ~m &
+                                0x80000000u) | ((unsigned)nslot & 0x7FFFFFFFu));
+        asm volatile("" : : "v"(code));  // keep it here, beside the wave minimum
+        key_min = wave_min_u32(key);
+        const bool mine = key == key_min;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(mine);
+        const int wl = __builtin_ctzll(mask);
+        const int wcode = readlane_i32(code, wl);
+        if (__builtin_expect(mask != (1ull << wl), 0)) return false;  // none, or equal high words
+        if (__builtin_expect((wcode ^ a_slot) != (int)0x80000000, 0)) {
+          // not plain, or the moved centre is in another bin, which is empty (a
+          // bin holds one centre): the old slot is emptied and the disk's meta
+          // word and slot index move (all lanes store the same; the centre is
+          // stored below)
+          if (wcode >= 0) return false;
+          const int ns = wcode & 0x7FFFFFFF;
+          pos[a_slot] = nan2;
+          meta[ns] = (uint32_t)a_lidx;
+          own_loc[a_lidx] = (uint16_t)ns;
+        }
+        if (REJ == 1) {  // log the lift (a full log is the general path's error)
+          if (n_undo == kUndoCap) return false;
+          undo_pos[n_undo] = make_double2(ax, ay);
+          undo_slot[n_undo] = make_int2(a_slot, wcode & 0x7FFFFFFF);
+          n_undo += 1;
+        }
         {
-          const uint64_t sb = (uint64_t)__double_as_longlong(best_s);
+          double2* const dst = mine ? pos + nslot : sink;  // the winning lane stores the moved centre
+          *dst = make_double2(nxl, nyl);
+        }
+        const double best_s = readlane_f64(s, wl);
+        const uint32_t wm = (uint32_t)readlane_i32((int)m, wl);
+        const double dacc = readlane_f64(fma(p.x - nxl, dx, (p.y - nyl) * dy), wl);
+        nrem = readlane_f64(left, wl);
+        a_slot = readlane_i32(widx, wl);
+        a_lidx = (int)wm;
+        __builtin_amdgcn_wave_barrier();
+        EC_WINDOW();
+        if (REJ == 1) {
+          chain_acc = chain_acc + dacc;
+          chain_lifts += 1;
+        } else {
+          acc = acc + dacc;
+        }
+        {
           // (the disk of a plain lift is not frozen: its meta word is its own
           // index, turned into its id when the records are hashed)
-          const uint32_t tag = ((uint32_t)EV_LIFT << 29) | wm;
-          writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32), tag, n_ring);
+          const uint64_t sb = (uint64_t)__double_as_longlong(best_s);
+          writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
+                     ((uint32_t)EV_LIFT << 29) | wm, n_ring);
         }
-        {
-          double2* const dst = (lane == 0) ? pos + a_loc : sink;
-          *dst = make_double2(nax, nay);
-        }
-        if (__builtin_expect(nslot != a_loc, 0)) {
-          // the moved centre crossed into another bin, which is empty (a bin
-          // holds one centre): lane 0 empties the old slot (over the store
-          // above: LDS stores of a wave land in order), lane 1 fills the new
-          // one, then lane 0 moves the meta word and lane 1 the slot index
-          double2* const dst = (lane == 0) ? pos + a_loc : ((lane == 1) ? pos + nslot : sink);
-          *dst = (lane == 0) ? nan2 : make_double2(nax, nay);
-          uint32_t* const dm = (lane == 0) ? meta + nslot : ((lane == 1) ? (uint32_t*)own_loc + a_lidx : sink32);
-          *dm = (lane == 0) ? (uint32_t)a_lidx : (uint32_t)nslot;
-        }
-        __builtin_amdgcn_wave_barrier();
-        acc = acc + fma(wpx - nax, dx, (wpy - nay) * dy);
-        rem = rem - best_s;
-        a_loc = w_slot;
-        a_lidx = (int)wm;
-        ax = wpx;
-        ay = wpy;
-        EC_WINDOW(w_bx, w_by, xneg, yneg);
-        widx = wbase + loff;
-        p = pos[widx];
-        m = meta[widx];
         if (__builtin_expect(++n_ring == kDigestBatch, 0)) {
-          h ^= digest_batch(rec_lo, rec_hi, rec_tag, lane, kDigestBatch, ring_first, own_gid);
-          if (REJ == 0) n_lift += count_lifts(rec_tag, lane, kDigestBatch);
-          ring_first += kDigestBatch;
-          n_ring = 0;
-          EC_POLL();
+          EC_FLUSH();
           if (stop != 0 || capped != 0) return false;
         }
-      }
-      }  // a disk in the window
-      return true;
+        return true;
       };
       for (;;) {
         if (__builtin_expect(!plain_event(), 0)) break;
         if (__builtin_expect(!plain_event(), 0)) break;
       }  // plain lifts
       if (stop != 0 || capped != 0) continue;  // leaves the event loop
+
+      // ---- any other event.  The nearest disk of the window:
+      double best_s = INFINITY, wpx = 0.0, wpy = 0.0;  // (a disk can be hit exactly when best_s is finite)
+      uint32_t wm = kFrozenBit;
+      int w_slot = 0;
+      if (key_min != 0xFFFFFFFFu) {
+        const int win = argmin_lane_slots(s, m, own_gid, key, key_min);
+        best_s = readlane_f64(s, win);
+        wm = (uint32_t)readlane_i32((int)m, win);
+        wpx = readlane_f64(p.x, win);
+        wpy = readlane_f64(p.y, win);
+        w_slot = readlane_i32(widx, win);
+      }
+      const double rem = -nrem;
+      // Where the move to the nearest disk, or by the length left if that is
+      // shorter, is one the window vouches for and ends eps inside the cell, it
+      // is the event (as for plain lifts): a contact or the chain end.
+      double step = fmin(best_s, rem);
+      double nax = fma(step, dx, ax), nay = fma(step, dy, ay);
+      int kind = best_s < rem ? ((wm & kFrozenBit) ? EV_FROZEN : EV_LIFT) : EV_END;
       {
-      // the mover's bin (the plain-lift loop carries only its slot)
-      int abx, aby;
-      slot_bin(a_loc, abx, aby);
-      EC_WALLS();
-      EC_DECIDE(true);
-      if (__builtin_expect(((packed >> 21) & 1) == 0, 0)) {
-        // the window cannot vouch for this event: exact search over every slot
-        double ls = INFINITY;
-        uint32_t lid = 0xFFFFFFFFu;
-        int lslot = -1;
-        for (int sl = lane; sl < nslots; sl += 64) {
-          const double2 q2 = pos[sl];
-          double s2;
-          if (contact(q2.x - ax, q2.y - ay, dx, dy, sig2, s2)) {
-            const uint32_t m2 = meta[sl];
-            const uint32_t i2 = (m2 & kFrozenBit) ? (m2 & ~kFrozenBit) : (uint32_t)own_gid[m2];
-            if (s2 < ls || (s2 == ls && i2 < lid)) { ls = s2; lid = i2; lslot = sl; }
+        const double wall = fmax(fabs(nax - mid), fabs(nay - mid)) - inner;
+        kind |= hi_word(step - dsafe) & hi_word(wall) & (int)0x80000000;
+      }
+      kind = uniform_i32(kind);
+      if (__builtin_expect(kind >= 0, 0)) {
+        // The full decision: distances to the walls of the cell ahead, (wall -
+        // v) / d as a product with 1/d, clamped at 0; first the nearest disk,
+        // then the x and the y wall, where strictly nearer.
+        const double idx = (dx != 0.0) ? 1.0 / dx : 1.0, idy = (dy != 0.0) ? 1.0 / dy : 1.0;
+        const double wallx = (dx > 0.0) ? w : ((dx < 0.0) ? 0.0 : INFINITY);
+        const double wally = (dy > 0.0) ? w : ((dy < 0.0) ? 0.0 : INFINITY);
+        double tx = (wallx - ax) * idx;
+        tx = (tx < 0.0) ? 0.0 : tx;
+        double ty = (wally - ay) * idy;
+        ty = (ty < 0.0) ? 0.0 : ty;
+#define EC_DECIDE()                                                                 \
+        do {                                                                        \
+          double e_ = best_s;                                                       \
+          kind = (wm & kFrozenBit) ? EV_FROZEN : EV_LIFT;                           \
+          if (tx < e_) { e_ = tx; kind = EV_WALL_X; }                               \
+          if (ty < e_) { e_ = ty; kind = EV_WALL_Y; }                               \
+          if (!(e_ < rem)) kind = EV_END;                                           \
+          kind = uniform_i32(kind);                                                 \
+          step = fmin(e_, rem);                                                     \
+        } while (0)
+        EC_DECIDE();
+        if (__builtin_expect(uniform_i32(step <= dsafe ? 1 : 0) == 0, 0)) {
+          // the window cannot vouch for this event: exact search over every slot
+          double ls = INFINITY;
+          uint32_t lid = 0xFFFFFFFFu;
+          int lslot = 0;
+          bool found = false;
+          for (int i = lane; i < nslots; i += 64) {
+            const int sl = i - qoff;
+            const double2 q2 = pos[sl];
+            double s2;
+            if (contact(q2.x - ax, q2.y - ay, dx, dy, sig2, s2)) {
+              const uint32_t m2 = meta[sl];
+              const uint32_t i2 = (m2 & kFrozenBit) ? (m2 & ~kFrozenBit) : (uint32_t)own_gid[m2];
+              if (s2 < ls || (s2 == ls && i2 < lid)) { ls = s2; lid = i2; lslot = sl; found = true; }
+            }
           }
+          const int fl = wave_argmin_all(ls, lid, found);
+          best_s = INFINITY;
+          wm = kFrozenBit;
+          if (fl >= 0) {
+            best_s = readlane_f64(ls, fl);
+            w_slot = readlane_i32(lslot, fl);
+            wm = (uint32_t)uniform_i32((int)meta[w_slot]);
+            // read into scalar registers here, so no load is left in flight
+            // where this rare path rejoins the event path
+            const double2 q2 = pos[w_slot];
+            wpx = readlane_f64(q2.x, 0);
+            wpy = readlane_f64(q2.y, 0);
+          }
+          EC_DECIDE();
         }
-        const int fl = wave_argmin_all(ls, lid, lslot >= 0);
-        best_s = INFINITY;
-        wm = kFrozenBit;
-        if (fl >= 0) {
-          best_s = readlane_f64(ls, fl);
-          w_slot = readlane_i32(lslot, fl);
-          wm = (uint32_t)uniform_i32((int)meta[w_slot]);
-          w_bx = w_slot % gridb;
-          w_by = w_slot / gridb;
-          // read into scalar registers here, so no load is left in flight
-          // where this rare path rejoins the event path
-          const double2 q2 = pos[w_slot];
-          wpx = readlane_f64(q2.x, 0);
-          wpy = readlane_f64(q2.y, 0);
-        }
-        EC_DECIDE(false);
-      }
 #undef EC_DECIDE
-#undef EC_WALLS
-      const int kind = (packed >> 16) & 7;
-      const bool ends = ((packed >> 20) & 1) != 0;
-      const int nbx = min(packed & 0xFF, nb + 1), nby = min((packed >> 8) & 0xFF, nb + 1);
-      // REJ 1: a wall or a frozen disk rejects the chain
-      const bool rejected = REJ == 1 && !ends && kind != EV_LIFT;
-      const double pax = ax, pay = ay;  // position before this event's move
-      ax = nax;
-      ay = nay;
-      // event record for the digest: bits of the step, kind << 29 | id (an own
-      // disk by its own index, turned into its id when the records are hashed)
-      const uint32_t eid = ends ? (uint32_t)end_id
-                                : (kind == EV_WALL_X ? (uint32_t)wall_x_id
-                                                     : (kind == EV_WALL_Y ? (uint32_t)wall_y_id
-                                                                          : (wm & ~kFrozenBit)));
-      {
-        // lane n_ring keeps this event's record (lane writes, no change of
-        // the execution mask)
-        const uint64_t sb = (uint64_t)__double_as_longlong(step);
-        const uint32_t tag = ((uint32_t)(ends ? EV_END : kind) << 29) | eid;
-        writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32), tag, n_ring);
+        nax = fma(step, dx, ax);
+        nay = fma(step, dy, ay);
       }
-      if (REJ == 1 && !rejected && !ends) {
-        // log the lift's move: slot before it and old position (the slot after
-        // it is known below); a full log stops the sweep with an error
-        if (n_undo == kUndoCap) {
-          if (lane == 0) atomicOr(d.err, ERR_UNDO_CAP);
-          stop = 1;
-        } else if (lane == 0) {
-          undo_pos[n_undo] = make_double2(pax, pay);
-          undo_slot[n_undo] = make_int2(a_loc, a_loc);
-        }
+      kind &= 7;
+      // bin of the moved centre, which lies in [0, w] up to rounding: truncation
+      // gives 0..nb-1, and nb on the far wall
+      const int ns = uniform_i32(min((int)(nay * inv_b), nb - 1) * gridb + min((int)(nax * inv_b), nb - 1));
+      // REJ 1: a wall or a frozen disk rejects the chain
+      const bool rejected = REJ == 1 && kind != EV_END && kind != EV_LIFT;
+      // event record for the digest: bits of the step, kind << 29 | id (an own
+      // disk by its own index, turned into its id when the records are hashed);
+      // lane n_ring keeps it (lane writes, no change of the execution mask)
+      {
+        const uint32_t eid = kind == EV_END ? (uint32_t)end_id
+                             : (kind == EV_WALL_X ? (uint32_t)wall_x_id
+                                                  : (kind == EV_WALL_Y ? (uint32_t)wall_y_id
+                                                                       : (wm & ~kFrozenBit)));
+        const uint64_t sb = (uint64_t)__double_as_longlong(step);
+        writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
+                   ((uint32_t)kind << 29) | eid, n_ring);
+      }
+      if (REJ == 1 && kind == EV_LIFT && n_undo == kUndoCap) {
+        // a full log stops the sweep with an error
+        if (lane == 0) atomicOr(d.err, ERR_UNDO_CAP);
+        stop = 1;
       }
       if (rejected) {
         // undo every logged lift, latest first: each disk goes back to the
@@ -1239,7 +1213,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
               const uint32_t mv = meta[sl.y];
               pos[sl.y] = nan2;
               meta[sl.x] = mv;
-              own_loc[(int)mv] = sl.x;
+              own_loc[(int)mv] = (uint16_t)sl.x;
             }
             pos[sl.x] = old;
           }
@@ -1247,103 +1221,82 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
         n_undo = 0;
         if (kind == EV_FROZEN) n_frozen += 1;
         else n_wall += 1;
-      } else
-      // store the moved disk; move it to another bin if it crossed a bin edge
-      if (nbx == abx && nby == aby) {
-        double2* const dst = (lane == 0) ? pos + a_loc : sink;
-        *dst = make_double2(ax, ay);
       } else {
-        const int ns = nby * gridb + nbx;
-        const bool free_ = __builtin_isnan(readlane_f64(pos[ns].x, 0));
-        if (__builtin_expect(!free_, 0)) {
-          if (lane == 0) {
-            atomicOr(d.err, ERR_BIN_CAP);
-            pos[a_loc] = make_double2(ax, ay);
-          }
-        } else {
-          if (lane == 0) {
-            pos[a_loc] = nan2;
-            pos[ns] = make_double2(ax, ay);
+        // store the moved disk (all lanes the same); move it to another bin if
+        // it crossed a bin edge
+        const int from = a_slot;
+        if (ns != a_slot) {
+          if (__builtin_expect(!__builtin_isnan(readlane_f64(pos[ns].x, 0)), 0)) {
+            if (lane == 0) atomicOr(d.err, ERR_BIN_CAP);
+          } else {
+            pos[a_slot] = nan2;
             meta[ns] = (uint32_t)a_lidx;
-            own_loc[a_lidx] = ns;
+            own_loc[a_lidx] = (uint16_t)ns;
+            a_slot = ns;
           }
-          a_loc = ns;
-          abx = nbx;
-          aby = nby;
         }
-      }
-      if (REJ == 1 && !rejected && !ends && stop == 0) {
-        if (lane == 0) undo_slot[n_undo].y = a_loc;  // the slot the disk now holds
-        n_undo += 1;
+        pos[a_slot] = make_double2(nax, nay);
+        if (REJ == 1 && kind == EV_LIFT && stop == 0) {
+          undo_pos[n_undo] = make_double2(ax, ay);
+          undo_slot[n_undo] = make_int2(from, a_slot);
+          n_undo += 1;
+        }
       }
       __builtin_amdgcn_wave_barrier();
-      if (__builtin_expect(++n_ring == kDigestBatch, 0)) {
-        h ^= digest_batch(rec_lo, rec_hi, rec_tag, lane, kDigestBatch, ring_first, own_gid);
-          if (REJ == 0) n_lift += count_lifts(rec_tag, lane, kDigestBatch);
-        ring_first += kDigestBatch;
-        n_ring = 0;
-        EC_POLL();
-      }
+      if (__builtin_expect(++n_ring == kDigestBatch, 0)) EC_FLUSH();
       if (rejected) {
         ended = 1;
-      } else if (!ends && kind == EV_LIFT) {
+      } else if (kind == EV_LIFT) {
         // straight chain: the hit disk goes on in the same direction
+        const double dacc = fma(wpx - nax, dx, (wpy - nay) * dy);
         if (REJ == 1) {
-          chain_acc = chain_acc + fma(wpx - ax, dx, (wpy - ay) * dy);
+          chain_acc = chain_acc + dacc;
           chain_lifts += 1;
         } else {
-          acc = acc + fma(wpx - ax, dx, (wpy - ay) * dy);
+          acc = acc + dacc;
         }
-        rem = rem - e;
-        a_loc = w_slot;
+        nrem = nrem + step;
+        a_slot = w_slot;
         a_lidx = (int)wm;
-        abx = w_bx;
-        aby = w_by;
-        ax = wpx;
-        ay = wpy;
-      } else if (__builtin_expect(ends, 0)) {
+      } else if (kind == EV_END) {
         ended = 1;
         if (REJ == 1) {  // accepted: its contact sum and lifts count
           acc = acc + chain_acc;
           n_lift += chain_lifts;
         }
       } else {
-        rem = rem - e;
+        nrem = nrem + step;
         if (__builtin_expect(kind == EV_FROZEN, 1)) {
-          // mirror the direction about the contact normal
-          const double rx = wpx - ax, ry = wpy - ay;
+          // mirror the direction about the contact normal (both square roots
+          // are correctly rounded; their arguments, about sigma^2 and 1, lie in
+          // the range of sqrt_contact)
+          const double rx = wpx - nax, ry = wpy - nay;
           acc = acc + fma(rx, dx, ry * dy);
           n_frozen += 1;
-          // (both square roots are correctly rounded; their arguments, about
-          // sigma^2 and 1, lie in the range of sqrt_contact)
-          const double nrm = sqrt_contact(fma(rx, rx, ry * ry));
-          const double nx = rx / nrm, ny = ry / nrm;
-          const double dn = fma(dx, nx, dy * ny);
-          const double tt = -2.0 * dn;
+          double nx, ny;
+          div_pair(rx, ry, sqrt_contact(fma(rx, rx, ry * ry)), nx, ny);
+          const double tt = -2.0 * fma(dx, nx, dy * ny);
           const double ux = fma(tt, nx, dx), uy = fma(tt, ny, dy);
-          const double mm = sqrt_contact(fma(ux, ux, uy * uy));
-          dx = ux / mm;
-          dy = uy / mm;
+          div_pair(ux, uy, sqrt_contact(fma(ux, ux, uy * uy)), dx, dy);
           EC_SET_DIRECTION();
         } else {
           // a wall: reverse the normal component of the direction
           n_wall += 1;
           if (kind == EV_WALL_X) {
-            dx = -dx; idx = -idx; idxw = -idxw; wallx = w - wallx; xneg ^= 1;
+            dx = -dx;
+            offx = -7 - offx;
           } else {
-            dy = -dy; idy = -idy; idyw = -idyw; wally = w - wally; yneg ^= 1;
+            dy = -dy;
+            offy = -7 - offy;
           }
         }
       }
       // window of the next event (the stores above are seen: LDS operations
       // of one wave complete in order)
-      EC_WINDOW(abx, aby, xneg, yneg);
-      widx = wbase + loff;
-      p = pos[widx];
-      m = meta[widx];
-      }
+      EC_WINDOW();
     }
 #undef EC_POLL
+#undef EC_FLUSH
     if (ended == 0) {
       // stopped by another wave's error, or this chain reached the event cap
       if (stop == 0 && lane == 0) {
@@ -1351,7 +1304,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
         if (atomicAdd(d.err + 1, 1) == 0) {
           double* g = d.dbg;
           g[0] = (double)cell; g[1] = (double)k; g[2] = (double)sweep; g[3] = (double)q;
-          g[4] = ax; g[5] = ay; g[6] = dx; g[7] = dy; g[8] = rem; g[9] = (double)a_loc;
+          g[4] = ax; g[5] = ay; g[6] = dx; g[7] = dy; g[8] = -nrem; g[9] = (double)a_slot;
           g[10] = (double)own_gid[a_lidx]; g[11] = (double)n_own;
         }
       }
@@ -1372,12 +1325,12 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // are published with the positions.  LDS: the meta words are free now and
   // hold the 9 region counts and the 9 fill cursors; own_loc takes each
   // disk's region once its slot has been read.
-  uint32_t* const rcnt = meta;
+  uint32_t* const rcnt = meta_all;
   if (lane < 2 * kRegions) rcnt[lane] = 0u;
   wave_sync();
   for (int k = lane; k < n_own; k += 64) {
     int g = own_gid[k];
-    double2 v = pos[own_loc[k]];
+    double2 v = pos[(int)own_loc[k]];
     double px = d.x[g], py = d.y[g];
     double v0x = local_coord(px, dr.sx, ox, L, half_L);
     double v0y = local_coord(py, dr.sy, oy, L, half_L);
@@ -1390,7 +1343,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
     // (from the cell-local position, which differs from the one a neighbour
     // computes from (nx, ny) by a few ulps of L, far inside the strip margin)
     const int r = 3 * strip_of(v.y, w, d.strip) + strip_of(v.x, w, d.strip);
-    own_loc[k] = r;
+    own_loc[k] = (uint16_t)r;
     atomicAdd(&rcnt[r], 1u);
   }
   wave_sync();
@@ -1404,7 +1357,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   }
   wave_sync();
   for (int k = lane; k < n_own; k += 64) {
-    const uint32_t at = atomicAdd(&rcnt[kRegions + own_loc[k]], 1u);
+    const uint32_t at = atomicAdd(&rcnt[kRegions + (int)own_loc[k]], 1u);
     d.cell_ids[at] = own_gid[k];
   }
   if (lane == 0) {
@@ -1421,7 +1374,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 
 // Colour phase q of a sweep: one launch per phase, one wavefront per active
 // cell; the launch boundary separates the phases.
-template <int PREC, int REJ>
+template <int REJ>
 __global__ void __launch_bounds__(256) k_phase(const Dev* __restrict__ ds, int q) {
   const Dev& d = ds[blockIdx.y];
   const int64_t sweep = *d.sweep_ctr;
@@ -1432,7 +1385,7 @@ __global__ void __launch_bounds__(256) k_phase(const Dev* __restrict__ ds, int q
   const int blk = blockIdx.x * d.cells_per_block + wave;
   if (blk >= half * half) return;  // the whole wave leaves; no workgroup barrier follows
   const SweepDraws dr = *d.draws;
-  phase_cell<PREC, REJ>(d, sweep, dr, q, blk, lds_raw + (size_t)wave * d.lds_per_cell, lane);
+  phase_cell<REJ>(d, sweep, dr, q, blk, lds_raw + (size_t)wave * d.lds_per_cell, lane);
 }
 
 // All four colour phases of a sweep in one launch.  The phases order only
@@ -1452,7 +1405,7 @@ __global__ void __launch_bounds__(256) k_phase(const Dev* __restrict__ ds, int q
 // ends.  Every wait is also bounded by d.dep_wait_ticks (100 MHz clock) and
 // abandoned when any wave has set d.err: on either, the wave sets or sees the
 // error and leaves, and the sweep reports it.
-template <int PREC, int REJ>
+template <int REJ>
 __global__ void __launch_bounds__(256) k_sweep_cells(const Dev* __restrict__ ds) {
   const Dev& d = ds[blockIdx.y];
   const int64_t sweep = *d.sweep_ctr;
@@ -1513,7 +1466,7 @@ __global__ void __launch_bounds__(256) k_sweep_cells(const Dev* __restrict__ ds)
       // the neighbours' write-backs are visible to the staging loads below
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    phase_cell<PREC, REJ>(d, sweep, dr, q, blk, base, lane);
+    phase_cell<REJ>(d, sweep, dr, q, blk, base, lane);
     // this cell's write-back before its flag
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (lane == 0)
@@ -1587,7 +1540,7 @@ __global__ void k_queue_prep(const Dev* __restrict__ ds, ReadyQueue rq) {
 // earlier-phase neighbours done, hence be published -- a contradiction.  Each
 // wait is also bounded (the first system's dep_wait_ticks) and given up once
 // any wave has flagged an abort.
-template <int PREC, int REJ>
+template <int REJ>
 __global__ void __launch_bounds__(256) k_queue_cells(const Dev* __restrict__ ds, ReadyQueue rq,
                                                      int lds_stride) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1637,7 +1590,7 @@ __global__ void __launch_bounds__(256) k_queue_cells(const Dev* __restrict__ ds,
     const int q = cell_phase(phase_of, d.C, cell);
     const int cx = cell % d.C, cy = cell / d.C;
     const int blk = (cy >> 1) * (d.C >> 1) + (cx >> 1);
-    phase_cell<PREC, REJ>(d, sweep, dr, q, blk, base, lane);
+    phase_cell<REJ>(d, sweep, dr, q, blk, base, lane);
     if (__builtin_amdgcn_readfirstlane(load_err(d)) != 0) {
       if (lane == 0) atomicExch(rq.hdr + QH_ABORT, 1);
       break;
@@ -2381,12 +2334,10 @@ hipError_t launch_zero_tallies(const Dev* ds, int32_t n_cells, hipStream_t st) {
 }
 
 hipError_t set_phase_lds_limit(int bytes) {
-  const void* fns[11] = {(const void*)k_phase<0, 0>,       (const void*)k_phase<1, 0>,
-                         (const void*)k_phase<0, 1>,       (const void*)k_sweep_cells<0, 0>,
-                         (const void*)k_sweep_cells<1, 0>, (const void*)k_sweep_cells<0, 1>,
-                         (const void*)k_queue_cells<0, 0>, (const void*)k_queue_cells<1, 0>,
-                         (const void*)k_queue_cells<0, 1>, (const void*)k_stripe_phase<0>,
-                         (const void*)k_periodic_bins};
+  const void* fns[8] = {(const void*)k_phase<0>,       (const void*)k_phase<1>,
+                        (const void*)k_sweep_cells<0>, (const void*)k_sweep_cells<1>,
+                        (const void*)k_queue_cells<0>, (const void*)k_queue_cells<1>,
+                        (const void*)k_stripe_phase<0>, (const void*)k_periodic_bins};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
@@ -2394,9 +2345,8 @@ hipError_t set_phase_lds_limit(int bytes) {
   return hipSuccess;
 }
 
-hipError_t ready_queue_workers(int lds_per_cell, int cpb, int fp32, int reject, int* workers) {
-  const void* f = fp32 ? (const void*)k_queue_cells<1, 0>
-                       : (reject ? (const void*)k_queue_cells<0, 1> : (const void*)k_queue_cells<0, 0>);
+hipError_t ready_queue_workers(int lds_per_cell, int cpb, int reject, int* workers) {
+  const void* f = reject ? (const void*)k_queue_cells<1> : (const void*)k_queue_cells<0>;
   int per_cu = 0, dev = 0, cus = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * cpb,
                                                               (size_t)cpb * lds_per_cell);
@@ -2468,14 +2418,11 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
                        st, ds, rq);
     const unsigned qgrid = (unsigned)((rq.workers + cpb - 1) / cpb);
     if (ev) (void)hipEventRecord(ev->begin[0], st);
-    if (sh.fp32_screen)
-      hipLaunchKernelGGL((k_queue_cells<1, 0>), dim3(qgrid), dim3(64 * cpb), lds, st, ds, rq,
-                         sh.max_lds_per_cell);
-    else if (sh.reject)
-      hipLaunchKernelGGL((k_queue_cells<0, 1>), dim3(qgrid), dim3(64 * cpb), lds, st, ds, rq,
+    if (sh.reject)
+      hipLaunchKernelGGL((k_queue_cells<1>), dim3(qgrid), dim3(64 * cpb), lds, st, ds, rq,
                          sh.max_lds_per_cell);
     else
-      hipLaunchKernelGGL((k_queue_cells<0, 0>), dim3(qgrid), dim3(64 * cpb), lds, st, ds, rq,
+      hipLaunchKernelGGL((k_queue_cells<0>), dim3(qgrid), dim3(64 * cpb), lds, st, ds, rq,
                          sh.max_lds_per_cell);
     if (ev) (void)hipEventRecord(ev->end[0], st);
     hipLaunchKernelGGL(k_queue_check, dim3(1, ns), dim3(64), 0, st, ds, rq);
@@ -2487,12 +2434,10 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
   if (sh.one_launch) {
     // as many wavefronts as one phase has cells; each takes cells of all phases
     if (ev) (void)hipEventRecord(ev->begin[0], st);
-    if (sh.fp32_screen)
-      hipLaunchKernelGGL((k_sweep_cells<1, 0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds);
-    else if (sh.reject)
-      hipLaunchKernelGGL((k_sweep_cells<0, 1>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds);
+    if (sh.reject)
+      hipLaunchKernelGGL((k_sweep_cells<1>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds);
     else
-      hipLaunchKernelGGL((k_sweep_cells<0, 0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds);
+      hipLaunchKernelGGL((k_sweep_cells<0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds);
     if (ev) (void)hipEventRecord(ev->end[0], st);
     hipError_t e = launch_check_overlap(ds, sh, st);
     if (e != hipSuccess) return e;
@@ -2501,12 +2446,10 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
   }
   for (int q = 0; q < 4; ++q) {
     if (ev) (void)hipEventRecord(ev->begin[q], st);
-    if (sh.fp32_screen)
-      hipLaunchKernelGGL((k_phase<1, 0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds, q);
-    else if (sh.reject)
-      hipLaunchKernelGGL((k_phase<0, 1>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds, q);
+    if (sh.reject)
+      hipLaunchKernelGGL((k_phase<1>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds, q);
     else
-      hipLaunchKernelGGL((k_phase<0, 0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds, q);
+      hipLaunchKernelGGL((k_phase<0>), dim3(grid, ns), dim3(64 * cpb), lds, st, ds, q);
     if (ev) (void)hipEventRecord(ev->end[q], st);
   }
   hipError_t e = launch_check_overlap(ds, sh, st);
