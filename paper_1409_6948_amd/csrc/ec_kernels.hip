@@ -262,28 +262,35 @@ __device__ __forceinline__ unsigned wave_xor_all(unsigned v) {
   return (unsigned)r32[0] ^ (unsigned)r32[1];
 }
 
-// Digest terms of the first `count` event records held one per lane (lane k:
-// record of event first + k, in three 32-bit registers: the step's bits and
-// kind << 29 | id, where a lift (kind 1) names its disk by the index into the
-// cell's id-ordered list own_gid), XOR-ed over the wave.
-__device__ __forceinline__ uint64_t digest_batch(uint32_t rec_lo, uint32_t rec_hi, uint32_t rec_tag,
-                                                 int lane, int count, uint64_t first,
-                                                 const int32_t* own_gid) {
+// Event records of a simulation cell: 64, three words each in a 16-byte LDS
+// slot, the step's bits and (kind ^ 1) << 29 | id, where a lift (kind 1) names
+// its disk by the index into the cell's id-ordered list own_gid (a lift's word
+// is then its disk's meta word).  XOR over the wave of the digest terms of the
+// first `count` records, record 0 being event `first`; lifts counts the lifts.
+constexpr int kRecSlot = 16;
+
+__device__ __forceinline__ uint64_t digest_records(const uint32_t* rec, int lane, int count,
+                                                   uint64_t first, const int32_t* own_gid,
+                                                   uint32_t& lifts) {
   uint64_t t = 0;
+  bool is_lift = false;
   if (lane < count) {
-    const uint64_t sb = ((uint64_t)rec_hi << 32) | rec_lo;
-    const int kind = (int)(rec_tag >> 29);
-    uint32_t id = rec_tag & 0x1FFFFFFFu;
-    if (kind == 1) id = (uint32_t)own_gid[id];
-    t = digest_term(kind, id, __longlong_as_double((long long)sb), first + (uint64_t)lane);
+    const uint4 r = *(const uint4*)(rec + (kRecSlot / 4) * lane);
+    is_lift = (r.z >> 29) == 0;
+    uint32_t id = r.z & 0x1FFFFFFFu;
+    if (is_lift) id = (uint32_t)own_gid[id];
+    t = digest_term((int)(r.z >> 29) ^ 1, id,
+                    __longlong_as_double((long long)(((uint64_t)r.y << 32) | r.x)), first + (uint64_t)lane);
   }
+  lifts = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(is_lift));
   const uint32_t lo = (uint32_t)uniform_i32((int)wave_xor_all((uint32_t)t));
   const uint32_t hi = (uint32_t)uniform_i32((int)wave_xor_all((uint32_t)(t >> 32)));
   return ((uint64_t)hi << 32) | lo;
 }
 
-// The same hash of records whose ids are the disks' own (no index to turn
-// into an id): the periodic cell's records.
+// The digest terms of the periodic cell's records, held one per lane (lane k:
+// record of event first + k, in three 32-bit registers: the step's bits and
+// kind << 29 | id).
 __device__ __forceinline__ uint64_t digest_batch_ids(uint32_t rec_lo, uint32_t rec_hi, uint32_t rec_tag,
                                                      int lane, int count, uint64_t first) {
   uint64_t t = 0;
@@ -729,6 +736,191 @@ __device__ __forceinline__ int32_t load_err(const Dev& d) {
   return __hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ---------------------------------------------------------------------------
+// The plain lifts of a chain, written out
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// A plain lift: the nearest disk in the window is not frozen and is hit within
+// the remaining length, the window vouches for the move, and the moved centre
+// stays inside the cell by eps on both axes, so neither wall comes first (with
+// the wall distance (wall - v) / d rounded as the full decision rounds it, a
+// centre that stops eps short of the wall leaves the wall farther by far more
+// than the rounding); the centre may change bin.  This is exactly the full
+// decision finding such a lift.  The loop runs them until the event found is
+// another one, or two distances agree to their high words (left to the general
+// path with nothing changed), or n_ring reaches the limit.
+//
+// Every lane tests its own disk, with the winner's own values, between the
+// steps of the wave minimum, whose results must wait two issue slots each.  The
+// lanes that hold the minimum (one, or the loop is left) become the execution
+// mask, and the winner stores the moved centre, the record, and what the next
+// event needs of it (length left, contact term), which all lanes read back with
+// the next window: an LDS store and a share of a wait that is there anyway cost
+// less than a lane read per word (5 to 9 cycles) and the lane index before it
+// (20).  Written out by hand because the compiler has no form for that mask, put
+// the loop's exits through flags, and places what can wait before the reads.
+// Registers are fixed: halves of a pair cannot be named otherwise.  Wait states
+// kept: 2 from a vector write to its use by a DPP step, or of a scalar or vcc to
+// a vector use; 1 to a lane read, or from the root estimate to its use.
+// Everything read from LDS has arrived where the code is left.
+// Measured: 1M disks 100.6 -> 88.2 ms a sweep against the same search compiled
+// from C++ (about 700 -> 600 cycles per plain lift), 4M disks 358 -> 321 ms.
+#define EC_PLAIN_LOOP(LOG, STEP, UNDO)                                                                     \
+  asm volatile(                                                                                \
+      "s_nop 4\n\t"                                                                            \
+      "1:\n\t"                                                                                 \
+      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
+      /* contact distance */                                                                   \
+      "v_add_f64 v[108:109], v[66:67], -v[72:73]\n\t"                                          \
+      "v_add_f64 v[110:111], v[64:65], -v[70:71]\n\t"                                          \
+      "v_mul_f64 v[112:113], v[108:109], -v[80:81]\n\t"                                        \
+      "v_mul_f64 v[114:115], v[82:83], v[108:109]\n\t"                                         \
+      "v_fmac_f64_e32 v[112:113], v[110:111], v[82:83]\n\t"                                    \
+      "v_fmac_f64_e32 v[114:115], v[110:111], v[80:81]\n\t"                                    \
+      "v_fma_f64 v[116:117], -v[112:113], v[112:113], %[sig2]\n\t"                             \
+      "v_rsq_f64_e32 v[118:119], v[116:117]\n\t"                                               \
+      "v_add_f64 v[78:79], v[78:79], v[76:77]\n\t"                                             \
+      "v_min_f64 v[112:113], v[114:115], v[116:117]\n\t"                                       \
+      "v_mul_f64 v[108:109], v[116:117], v[118:119]\n\t"                                       \
+      "v_mul_f64 v[118:119], v[118:119], 0.5\n\t"                                              \
+      "v_cmp_lt_f64_e32 vcc, 0, v[112:113]\n\t"                                                \
+      "v_fma_f64 v[110:111], -v[118:119], v[108:109], 0.5\n\t"                                 \
+      "v_fmac_f64_e32 v[108:109], v[108:109], v[110:111]\n\t"                                  \
+      "v_fmac_f64_e32 v[118:119], v[118:119], v[110:111]\n\t"                                  \
+      "v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]\n\t"                          \
+      "v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]\n\t"                                  \
+      "v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]\n\t"                          \
+      "v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]\n\t"                                  \
+      "v_add_f64 v[96:97], v[114:115], -v[108:109]\n\t"                                        \
+      "v_max_f64 v[96:97], v[96:97], 0\n\t"                                                    \
+      "v_cndmask_b32_e32 v120, -1, v97, vcc\n\t"                                               \
+      /* moved centre, tests and wave minimum */                                               \
+      "v_fma_f64 v[104:105], v[96:97], v[80:81], v[70:71]\n\t"                                 \
+      "v_fma_f64 v[106:107], v[96:97], v[82:83], v[72:73]\n\t"                                 \
+      "v_min_u32_dpp v121, v120, v120 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"      \
+      "v_add_f64 v[108:109], v[104:105], -%[mid]\n\t"                                          \
+      "v_add_f64 v[110:111], v[106:107], -%[mid]\n\t"                                          \
+      "v_min_u32_dpp v121, v121, v121 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"      \
+      "v_max_f64 v[108:109], |v[108:109]|, |v[110:111]|\n\t"                                   \
+      "v_mul_f64 v[112:113], v[106:107], %[inv_b]\n\t"                                         \
+      "v_min_u32_dpp v121, v121, v121 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"          \
+      "v_mul_f64 v[114:115], v[104:105], %[inv_b]\n\t"                                         \
+      "v_cvt_i32_f64_e32 v112, v[112:113]\n\t"                                                 \
+      "v_min_u32_dpp v121, v121, v121 row_mirror row_mask:0xf bank_mask:0xf\n\t"               \
+      "v_cvt_i32_f64_e32 v114, v[114:115]\n\t"                                                 \
+      "v_add_f64 v[108:109], v[108:109], -%[inner]\n\t"                                        \
+      "v_min_u32_dpp v121, v121, v121 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"             \
+      "v_mad_u32_u24 v123, v112, %[gridb], v114\n\t"                                           \
+      "v_add_f64 v[100:101], v[96:97], v[74:75]\n\t"                                           \
+      "v_min_u32_dpp v121, v121, v121 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"             \
+      "v_add_f64 v[110:111], v[96:97], -v[84:85]\n\t"                                          \
+      "v_and_b32_e32 v122, v101, v109\n\t"                                                     \
+      "v_readlane_b32 %[kmin], v121, 63\n\t"                                                   \
+      "v_bitop3_b32 v122, v122, v111, v98 bitop3:0x40\n\t" /* a & b & ~c */                    \
+      "v_bfi_b32 v122, %[low31], v123, v122\n\t"                                               \
+      "v_cmp_eq_u32_e64 %[mask], %[kmin], v120\n\t"                                            \
+      "v_add_f64 v[108:109], v[64:65], -v[104:105]\n\t"                                        \
+      "v_add_f64 v[110:111], v[66:67], -v[106:107]\n\t"                                        \
+      "v_mul_f64 v[102:103], v[82:83], v[110:111]\n\t"                                         \
+      "v_fmac_f64_e32 v[102:103], v[108:109], v[80:81]\n\t"                                    \
+      "v_lshl_add_u32 v124, v123, 4, %[pos]\n\t"                                               \
+      /* from here the winner alone */                                                         \
+      "s_mov_b64 exec, %[mask]\n\t"                                                            \
+      "v_readfirstlane_b32 %[t], v122\n\t"                                                     \
+      "v_readfirstlane_b32 %[slot], v69\n\t"                                                   \
+      "s_bcnt1_i32_b64 %[u], %[mask]\n\t"                                                      \
+      "ds_write_b96 v94, v[96:98]\n\t"                                                         \
+      "ds_write_b128 %[mail], v[100:103]\n\t"                                                  \
+      "s_cmp_lg_u32 %[u], 1\n\t"                                                               \
+      "s_cbranch_scc1 2f\n\t"                                                                  \
+      "s_xor_b32 %[u], %[t], %[a_slot]\n\t"                                                    \
+      "s_cmp_lg_u32 %[u], 0x80000000\n\t"                                                      \
+      "s_cbranch_scc1 3f\n\t"                                                                  \
+      "4:\n\t"                                                                                 \
+      "ds_write_b128 v124, v[104:107]\n\t"                                                     \
+      "v_readfirstlane_b32 %[a_lidx], v98\n\t"                                                 \
+      LOG                                                                                      \
+      "s_mov_b64 exec, -1\n\t"                                                                 \
+      STEP                                                                                     \
+      /* the next window: rows clamped to the grid */                                          \
+      "s_mov_b32 %[a_slot], %[slot]\n\t"                                                       \
+      "s_mul_i32 %[t], %[slot], %[inv_g20]\n\t"                                                \
+      "s_lshr_b32 %[t], %[t], 20\n\t"                                                          \
+      "s_add_i32 %[u], %[t], %[offy]\n\t"                                                      \
+      "s_min_i32 %[u], %[u], %[top]\n\t"                                                       \
+      "s_max_i32 %[u], %[u], -2\n\t"                                                           \
+      "s_sub_i32 %[u], %[u], %[t]\n\t"                                                         \
+      "s_mul_i32 %[u], %[u], %[gridb]\n\t"                                                     \
+      "s_add_i32 %[u], %[u], %[slot]\n\t"                                                      \
+      "v_add_u32_e32 v69, %[u], %[woff]\n\t"                                                   \
+      "v_lshl_add_u32 v125, v69, 4, %[pos]\n\t"                                                \
+      "v_lshl_add_u32 v126, v69, 2, %[meta]\n\t"                                               \
+      "ds_read_b128 v[64:67], v125\n\t"                                                        \
+      "ds_read_b32 v98, v126\n\t"                                                              \
+      "v_lshl_add_u32 v125, %[slot], 4, %[pos]\n\t"                                            \
+      "ds_read_b128 v[70:73], v125\n\t"                                                        \
+      "ds_read_b128 v[74:77], %[mail]\n\t"                                                     \
+      "v_add_u32_e32 v94, 16, v94\n\t"                                                         \
+      "s_add_i32 %[n_ring], %[n_ring], 1\n\t"                                                  \
+      "s_cmp_lg_u32 %[n_ring], %[limit]\n\t"                                                   \
+      "s_cbranch_scc1 1b\n\t"                                                                  \
+      "s_mov_b32 %[full], 1\n\t"                                                               \
+      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
+      "v_add_f64 v[78:79], v[78:79], v[76:77]\n\t"                                             \
+      "s_branch 5f\n\t"                                                                        \
+      /* not plain, or the moved centre is in another bin, which is empty (a bin holds one */  \
+      /* centre): the old slot is emptied, and the disk's meta word and slot index move    */  \
+      "3:\n\t"                                                                                 \
+      "s_cmp_ge_i32 %[t], 0\n\t"                                                               \
+      "s_cbranch_scc1 2f\n\t"                                                                  \
+      "v_mov_b32_e32 v108, 0\n\t"                                                              \
+      "v_mov_b32_e32 v109, 0x7ff80000\n\t"                                                     \
+      "v_mov_b32_e32 v110, 0\n\t"                                                              \
+      "v_mov_b32_e32 v111, 0x7ff80000\n\t"                                                     \
+      "v_lshl_add_u32 v125, %[a_slot], 4, %[pos]\n\t"                                          \
+      "ds_write_b128 v125, v[108:111]\n\t"                                                     \
+      "v_lshl_add_u32 v125, v123, 2, %[meta]\n\t"                                              \
+      "v_mov_b32_e32 v126, %[a_lidx]\n\t"                                                      \
+      "ds_write_b32 v125, v126\n\t"                                                            \
+      "v_lshl_add_u32 v125, %[a_lidx], 1, %[own_loc]\n\t"                                      \
+      "ds_write_b16 v125, v123\n\t"                                                            \
+      "s_branch 4b\n\t"                                                                        \
+      "2:\n\t"                                                                                 \
+      "s_mov_b64 exec, -1\n\t"                                                                 \
+      "s_mov_b32 %[full], 0\n\t"                                                               \
+      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
+      "5:\n\t"                                                                                 \
+      "s_nop 4"                                                                                \
+      : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(widx), "+{v[70:71]}"(ax),             \
+        "+{v[72:73]}"(ay), "+{v[74:75]}"(nrem), "+{v[76:77]}"(dacc), "+{v[78:79]}"(sum),       \
+        "+{v94}"(rec_at), "+{v98}"(m), "={v[96:97]}"(s), "={v120}"(key),                       \
+        [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+s"(a_slot),                      \
+        [a_lidx] "+s"(a_lidx), [n_ring] "+s"(n_ring), [mask] "=&s"(a_mask), [t] "=&s"(a_t),    \
+        [u] "=&s"(a_u), [slot] "=&s"(a_next) UNDO                                              \
+      : "{v[80:81]}"(dx), "{v[82:83]}"(dy), "{v[84:85]}"(guard), [pos] "v"(pos_at),            \
+        [meta] "v"(meta_at), [own_loc] "v"(own_loc_at), [mail] "v"(mail_at),                   \
+        [woff] "v"(loff + offx), [mid] "s"(mid), [inner] "s"(inner), [sig2] "s"(s_sig2),       \
+        [inv_b] "s"(s_inv_b), [gridb] "s"(s_gridb), [inv_g20] "s"(s_inv_g20),                  \
+        [offy] "s"(uniform_i32(offy)), [top] "s"(s_top), [limit] "s"(uniform_i32(limit)),      \
+        [low31] "s"(0x7FFFFFFF)                                                                \
+      : "vcc", "scc", "memory", "v100", "v101", "v102", "v103", "v104", "v105", "v106",        \
+        "v107", "v108", "v109", "v110", "v111", "v112", "v113", "v114", "v115", "v116",        \
+        "v117", "v118", "v119", "v121", "v122", "v123", "v124", "v125", "v126", "v127")
+// The rejection variant's undo log of a plain lift: slots before and after, old
+// position; then the next entry's addresses.
+#define EC_UNDO_LOG                                                                            \
+  "v_mov_b32_e32 v126, %[a_slot]\n\t"                                                          \
+  "v_mov_b32_e32 v127, v123\n\t"                                                               \
+  "ds_write_b64 %[uslot], v[126:127]\n\t"                                                      \
+  "ds_write_b128 %[upos], v[70:73]\n\t"
+#define EC_UNDO_STEP                                                                           \
+  "v_add_u32_e32 %[uslot], 8, %[uslot]\n\t"                                                    \
+  "v_add_u32_e32 %[upos], 16, %[upos]\n\t"
+#define EC_UNDO_OPERANDS , [uslot] "+v"(uslot_at), [upos] "+v"(upos_at)
+
 // Both components of (x, y) / den: the compiler's own FP64 division sequence
 // (reciprocal estimate, two Newton steps, quotient, one correction with the
 // exact residual), with the reciprocal formed once and without the range
@@ -761,13 +953,8 @@ __device__ __forceinline__ int hi_word(double v) {
 // things cost more: a scalar instruction that reads what a vector one has just
 // written (about 15 cycles of waiting), a branch (10 cycles not taken, 25
 // taken), the FP64 reciprocal square root (16) and the LDS round trip (60 for
-// the reads, 90 behind a store).  So the plain event below makes its tests in
-// vector registers as sign bits that are ANDed into one word, reads that word
-// once; everything the next window's address does not need stands behind the
-// read.  Measured: 1M disks (one wavefront per SIMD) 122.9 -> 100.6 ms a sweep
-// against tests made by compares joined in scalar registers, with the whole
-// window clamped and the moved centre recomputed from the winner's distance;
-// 16 x 16 cells of 64 disks 16.8 -> 13.4 ms.
+// the reads, 90 behind a store).  So plain lifts (above) make their tests in
+// vector registers as sign bits that are ANDed into one word and read once.
 template <int REJ>
 __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, const SweepDraws& dr,
                                            const int q, const int blk, unsigned char* const base,
@@ -799,9 +986,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // the id staging buffer of the rank sort lies in the position slots, which
   // are filled only after the sort
   int32_t* tmp = (int32_t*)(base + lay.off_pos);
-  // per-lane sink slots: lanes that have nothing to store write here, so a
-  // store by one lane needs no change of the execution mask
-  double2* const sink = (double2*)(base + lay.off_sink) + lane;
+  uint32_t* const rec = (uint32_t*)(base + lay.off_rec);  // event records of the digest
   // REJ 1 only: per logged lift the old position, then (slot before, slot after)
   double2* undo_pos = (double2*)(base + lay.off_undo);
   int2* undo_slot = (int2*)(undo_pos + kUndoCap);
@@ -898,9 +1083,11 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   double acc = d.acc_delta[cell];
   uint32_t n_lift = 0, n_frozen = 0, n_wall = 0;
   uint64_t h = 0;
-  int n_ring = 0;            // event records held in the lanes (lane k: record k)
+  int n_ring = 0;            // event records held
   uint64_t ring_first = 0;    // digest index of record 0
-  uint32_t rec_lo = 0, rec_hi = 0, rec_tag = 0;
+  // LDS addresses of the plain-lift loop
+  const uint32_t pos_at = lds_address(pos), meta_at = lds_address(meta), own_loc_at = lds_address(own_loc),
+                 mail_at = lds_address(base + lay.off_mail), rec_base = lds_address(rec);
   // lane = lx + 8 ly: one bin of an 8 x 8 window per lane, a window row in 8
   // neighbouring lanes
   const int loff = (lane >> 3) * gridb + (lane & 7);  // this lane's slot inside a window
@@ -919,7 +1106,10 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   const double reach = 5.0 * d.b - sigma - eps;
   // a plain lift keeps the moved centre in [eps, w - eps] on both axes, that is
   // |v - mid| < inner (see there)
-  const double mid = 0.5 * w, inner = 0.5 * w - eps;
+  // (the loop's scalar operands, read as such)
+  const double mid = readlane_f64(0.5 * w, 0), inner = readlane_f64(0.5 * w - eps, 0);
+  const double s_sig2 = readlane_f64(sig2, 0), s_inv_b = readlane_f64(inv_b, 0);
+  const int s_gridb = uniform_i32(gridb), s_inv_g20 = uniform_i32((int)inv_g20), s_top = uniform_i32(nb - 6);
   const bool use_window = d.search == 0;
   const uint64_t wall_x_id = (uint64_t)d.n, wall_y_id = (uint64_t)d.n + 1, end_id = (uint64_t)d.n + 3;
   int aborted = 0;
@@ -985,8 +1175,9 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
     } while (0)
 #define EC_FLUSH()                                                                  \
     do {                                                                            \
-      h ^= digest_batch(rec_lo, rec_hi, rec_tag, lane, kDigestBatch, ring_first, own_gid); \
-      if (REJ == 0) n_lift += count_lifts(rec_tag, lane, kDigestBatch);             \
+      uint32_t lifts_;                                                              \
+      h ^= digest_records(rec, lane, kDigestBatch, ring_first, own_gid, lifts_);    \
+      if (REJ == 0) n_lift += lifts_;                                               \
       ring_first += kDigestBatch;                                                   \
       n_ring = 0;                                                                   \
       EC_POLL();                                                                    \
@@ -1005,96 +1196,37 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       // contact distance of the disk in this lane's window slot, its high word
       // (all ones: no contact) and the wave minimum of those
       double s;
-      unsigned key, key_min;
-      // One plain lift: the nearest disk in the window is not frozen and is hit
-      // within the remaining length, the window vouches for the move, and the
-      // moved centre stays inside the cell by eps on both axes, so neither wall
-      // comes first (with the wall distance (wall - v) / d rounded as the full
-      // decision rounds it, a centre that stops eps short of the wall leaves
-      // the wall farther by far more than the rounding); the centre may change
-      // bin.  This is exactly the full decision finding such a lift; every
-      // other event, and two disks whose distances agree to their high words,
-      // are left to the general path with nothing changed (false), as is the
-      // way out after a poll that stops the chain.  Every lane tests its own
-      // disk, with the winner's own values, between the steps of the wave
-      // minimum, whose results must wait two issue slots each.  The loop runs
-      // two per pass, so that the common event takes a taken branch only every
-      // other time; every return is a constant, so each exit is a plain branch.
-      auto plain_event = [&]() __attribute__((always_inline)) -> bool {
-        const double rx = p.x - ax, ry = p.y - ay;
-        const double ca = fma(rx, dx, ry * dy);
-        const double cc = fma(rx, dy, -(ry * dx));
-        const double disc = fma(-cc, cc, sig2);
-        // (a root of a negative number or of an empty slot's NaN is NaN, and
-        // such a lane no candidate; the larger of NaN and 0 is 0)
-        s = fmax(ca - sqrt_contact(disc), 0.0);
-        key = fmin(ca, disc) > 0.0 ? (unsigned)hi_word(s) : 0xFFFFFFFFu;
-        const double nxl = fma(s, dx, ax), nyl = fma(s, dy, ay);
-        const double left = s + nrem;  // minus the length left after this lift
-        const double wall = fmax(fabs(nxl - mid), fabs(nyl - mid)) - inner;
-        const int nslot = (int)(nyl * inv_b) * gridb + (int)(nxl * inv_b);
-        // sign bit: plain; below it the slot of the moved centre
-        const int code = (int)(((unsigned)(hi_word(left) & hi_word(s - dsafe) & hi_word(wall)) & ~m &
-                                0x80000000u) | ((unsigned)nslot & 0x7FFFFFFFu));
-        asm volatile("" : : "v"(code));  // keep it here, beside the wave minimum
-        key_min = wave_min_u32(key);
-        const bool mine = key == key_min;
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(mine);
-        const int wl = __builtin_ctzll(mask);
-        const int wcode = readlane_i32(code, wl);
-        if (__builtin_expect(mask != (1ull << wl), 0)) return false;  // none, or equal high words
-        if (__builtin_expect((wcode ^ a_slot) != (int)0x80000000, 0)) {
-          // not plain, or the moved centre is in another bin, which is empty (a
-          // bin holds one centre): the old slot is emptied and the disk's meta
-          // word and slot index move (all lanes store the same; the centre is
-          // stored below)
-          if (wcode >= 0) return false;
-          const int ns = wcode & 0x7FFFFFFF;
-          pos[a_slot] = nan2;
-          meta[ns] = (uint32_t)a_lidx;
-          own_loc[a_lidx] = (uint16_t)ns;
-        }
-        if (REJ == 1) {  // log the lift (a full log is the general path's error)
-          if (n_undo == kUndoCap) return false;
-          undo_pos[n_undo] = make_double2(ax, ay);
-          undo_slot[n_undo] = make_int2(a_slot, wcode & 0x7FFFFFFF);
-          n_undo += 1;
-        }
-        {
-          double2* const dst = mine ? pos + nslot : sink;  // the winning lane stores the moved centre
-          *dst = make_double2(nxl, nyl);
-        }
-        const double best_s = readlane_f64(s, wl);
-        const uint32_t wm = (uint32_t)readlane_i32((int)m, wl);
-        const double dacc = readlane_f64(fma(p.x - nxl, dx, (p.y - nyl) * dy), wl);
-        nrem = readlane_f64(left, wl);
-        a_slot = readlane_i32(widx, wl);
-        a_lidx = (int)wm;
-        __builtin_amdgcn_wave_barrier();
-        EC_WINDOW();
-        if (REJ == 1) {
-          chain_acc = chain_acc + dacc;
-          chain_lifts += 1;
-        } else {
-          acc = acc + dacc;
-        }
-        {
-          // (the disk of a plain lift is not frozen: its meta word is its own
-          // index, turned into its id when the records are hashed)
-          const uint64_t sb = (uint64_t)__double_as_longlong(best_s);
-          writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
-                     ((uint32_t)EV_LIFT << 29) | wm, n_ring);
-        }
-        if (__builtin_expect(++n_ring == kDigestBatch, 0)) {
-          EC_FLUSH();
-          if (stop != 0 || capped != 0) return false;
-        }
-        return true;
-      };
+      uint32_t key, key_min;
+      // plain lifts, up to the next digest of 64 records
       for (;;) {
-        if (__builtin_expect(!plain_event(), 0)) break;
-        if (__builtin_expect(!plain_event(), 0)) break;
-      }  // plain lifts
+        const int before = n_ring;
+        double sum = REJ == 1 ? chain_acc : acc, dacc = 0.0, guard = dsafe;
+        int limit = kDigestBatch, full, a_t, a_u, a_next;
+        uint64_t a_mask;
+        uint32_t rec_at = rec_base + (uint32_t)(kRecSlot * n_ring);
+        a_slot = uniform_i32(a_slot);
+        a_lidx = uniform_i32(a_lidx);
+        n_ring = uniform_i32(n_ring);
+        if (REJ == 1) {
+          // the log's end is a limit too; with a full log no lift is plain
+          // (whose move would be the general path's error)
+          if (n_undo == kUndoCap) guard = -1.0;
+          else limit = min(limit, n_ring + kUndoCap - n_undo);
+          uint32_t upos_at = lds_address(undo_pos + n_undo), uslot_at = lds_address(undo_slot + n_undo);
+          EC_PLAIN_LOOP(EC_UNDO_LOG, EC_UNDO_STEP, EC_UNDO_OPERANDS);
+          chain_acc = sum;
+          n_undo += n_ring - before;
+          chain_lifts += (uint32_t)(n_ring - before);
+        } else {
+          EC_PLAIN_LOOP("", "", );
+          acc = sum;
+        }
+        if (full == 0) break;
+        if (n_ring == kDigestBatch) {
+          EC_FLUSH();
+          if (stop != 0 || capped != 0) break;
+        }
+      }
       if (stop != 0 || capped != 0) continue;  // leaves the event loop
 
       // ---- any other event.  The nearest disk of the window:
@@ -1184,17 +1316,15 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       const int ns = uniform_i32(min((int)(nay * inv_b), nb - 1) * gridb + min((int)(nax * inv_b), nb - 1));
       // REJ 1: a wall or a frozen disk rejects the chain
       const bool rejected = REJ == 1 && kind != EV_END && kind != EV_LIFT;
-      // event record for the digest: bits of the step, kind << 29 | id (an own
-      // disk by its own index, turned into its id when the records are hashed);
-      // lane n_ring keeps it (lane writes, no change of the execution mask)
       {
+        // event record for the digest (all lanes store the same)
         const uint32_t eid = kind == EV_END ? (uint32_t)end_id
                              : (kind == EV_WALL_X ? (uint32_t)wall_x_id
                                                   : (kind == EV_WALL_Y ? (uint32_t)wall_y_id
                                                                        : (wm & ~kFrozenBit)));
         const uint64_t sb = (uint64_t)__double_as_longlong(step);
-        writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
-                   ((uint32_t)kind << 29) | eid, n_ring);
+        *(uint4*)(rec + (kRecSlot / 4) * n_ring) =
+            make_uint4((uint32_t)sb, (uint32_t)(sb >> 32), ((uint32_t)(kind ^ 1) << 29) | eid, 0u);
       }
       if (REJ == 1 && kind == EV_LIFT && n_undo == kUndoCap) {
         // a full log stops the sweep with an error
@@ -1316,8 +1446,9 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 
   // ---- write back: old position + local displacement, wrapped --------------
   wave_sync();
-  h ^= digest_batch(rec_lo, rec_hi, rec_tag, lane, n_ring, ring_first, own_gid);
-  if (REJ == 0) n_lift += count_lifts(rec_tag, lane, n_ring);
+  uint32_t last_lifts;
+  h ^= digest_records(rec, lane, n_ring, ring_first, own_gid, last_lifts);
+  if (REJ == 0) n_lift += last_lifts;
   // The cell's id list is sorted again by the regions of the moved disks:
   // the neighbours of later colour phases stage their frozen band from the
   // regions that face them.  The list keeps its range [start, start + n_own)
