@@ -137,11 +137,10 @@ struct Dev {
 // position, 32-bit meta word: own index, or frozen id | top bit), with
 // kSlotPad empty slots before the first and after the last (a window's columns
 // are not clamped to the grid); the cell's id-ordered list and the 16-bit slot
-// of each own disk (at most 100^2 slots); the records of 64 events; what one
-// event leaves for the next.
+// of each own disk (at most 100^2 slots).
 constexpr int kSlotPad = 3;
 struct CellLds {
-  int32_t off_pos, off_meta, off_own_gid, off_own_loc, off_rec, off_mail, off_undo, bytes;
+  int32_t off_pos, off_meta, off_own_gid, off_own_loc, off_undo, bytes;
 };
 
 // reject: an undo log of kUndoCap entries (slots and old position, 32 B each).
@@ -155,8 +154,6 @@ __host__ __device__ inline CellLds cell_lds_layout(int gridb, int cap_own, bool 
   l.off_own_gid = o;  o += 4 * cap_own;
   l.off_own_loc = o;  o += 2 * cap_own;
   o = (o + 15) & ~15;
-  l.off_rec = o;      o += 16 * 64;
-  l.off_mail = o;     o += 16;
   l.off_undo = o;     o += reject ? 32 * kUndoCap : 0;
   l.bytes = (o + 15) & ~15;
   return l;

@@ -262,25 +262,23 @@ __device__ __forceinline__ unsigned wave_xor_all(unsigned v) {
   return (unsigned)r32[0] ^ (unsigned)r32[1];
 }
 
-// Event records of a simulation cell: 64, three words each in a 16-byte LDS
-// slot, the step's bits and (kind ^ 1) << 29 | id, where a lift (kind 1) names
-// its disk by the index into the cell's id-ordered list own_gid (a lift's word
-// is then its disk's meta word).  XOR over the wave of the digest terms of the
-// first `count` records, record 0 being event `first`; lifts counts the lifts.
-constexpr int kRecSlot = 16;
-
-__device__ __forceinline__ uint64_t digest_records(const uint32_t* rec, int lane, int count,
-                                                   uint64_t first, const int32_t* own_gid,
-                                                   uint32_t& lifts) {
+// Event records of a simulation cell, held one per lane (lane k: record of
+// event first + k, in three 32-bit registers): the step's bits and (kind ^ 1)
+// << 29 | id, where a lift (kind 1) names its disk by the index into the cell's
+// id-ordered list own_gid (a lift's word is then its disk's meta word).  XOR
+// over the wave of the digest terms of the first `count`; lifts counts the
+// lifts among them.
+__device__ __forceinline__ uint64_t digest_records(uint32_t rec_lo, uint32_t rec_hi, uint32_t rec_tag,
+                                                   int lane, int count, uint64_t first,
+                                                   const int32_t* own_gid, uint32_t& lifts) {
   uint64_t t = 0;
   bool is_lift = false;
   if (lane < count) {
-    const uint4 r = *(const uint4*)(rec + (kRecSlot / 4) * lane);
-    is_lift = (r.z >> 29) == 0;
-    uint32_t id = r.z & 0x1FFFFFFFu;
+    is_lift = (rec_tag >> 29) == 0;
+    uint32_t id = rec_tag & 0x1FFFFFFFu;
     if (is_lift) id = (uint32_t)own_gid[id];
-    t = digest_term((int)(r.z >> 29) ^ 1, id,
-                    __longlong_as_double((long long)(((uint64_t)r.y << 32) | r.x)), first + (uint64_t)lane);
+    t = digest_term((int)(rec_tag >> 29) ^ 1, id,
+                    __longlong_as_double((long long)(((uint64_t)rec_hi << 32) | rec_lo)), first + (uint64_t)lane);
   }
   lifts = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(is_lift));
   const uint32_t lo = (uint32_t)uniform_i32((int)wave_xor_all((uint32_t)t));
@@ -737,7 +735,7 @@ __device__ __forceinline__ int32_t load_err(const Dev& d) {
 }
 
 // ---------------------------------------------------------------------------
-// The plain lifts of a chain, written out
+// The plain lifts and reflections of a chain, written out
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
@@ -749,176 +747,300 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // the wall distance (wall - v) / d rounded as the full decision rounds it, a
 // centre that stops eps short of the wall leaves the wall farther by far more
 // than the rounding); the centre may change bin.  This is exactly the full
-// decision finding such a lift.  The loop runs them until the event found is
-// another one, or two distances agree to their high words (left to the general
-// path with nothing changed), or n_ring reaches the limit.
+// decision finding such a lift.  A plain reflection is the same with a frozen
+// disk.  The loop runs both (the rejection variant: lifts only) until the event
+// found is another one, or two distances agree to their high words (left to the
+// general path with nothing changed), or n_ring reaches the limit.
 //
 // Every lane tests its own disk, with the winner's own values, between the
 // steps of the wave minimum, whose results must wait two issue slots each.  The
 // lanes that hold the minimum (one, or the loop is left) become the execution
-// mask, and the winner stores the moved centre, the record, and what the next
-// event needs of it (length left, contact term), which all lanes read back with
-// the next window: an LDS store and a share of a wait that is there anyway cost
-// less than a lane read per word (5 to 9 cycles) and the lane index before it
-// (20).  Written out by hand because the compiler has no form for that mask, put
-// the loop's exits through flags, and places what can wait before the reads.
+// mask: the winner stores the moved centre itself, and a lane read is then a
+// first-lane read, without the lane's index.  What the next window's address
+// does not need stands behind its reads.  A reflection is computed in the
+// winner's lane, beside the loop, and comes back into it.
+// Written out by hand because the compiler has no form for that mask, puts the
+// loop's exits through flags, and places what can wait before the reads.
 // Registers are fixed: halves of a pair cannot be named otherwise.  Wait states
 // kept: 2 from a vector write to its use by a DPP step, or of a scalar or vcc to
-// a vector use; 1 to a lane read, or from the root estimate to its use.
-// Everything read from LDS has arrived where the code is left.
-// Measured: 1M disks 100.6 -> 88.2 ms a sweep against the same search compiled
-// from C++ (about 700 -> 600 cycles per plain lift), 4M disks 358 -> 321 ms.
-#define EC_PLAIN_LOOP(LOG, STEP, UNDO)                                                                     \
+// a vector use; 1 to a lane read, or from a root or reciprocal estimate to its
+// use.  Everything read from LDS has arrived where the code is left.
+//
+// Costs found by doubling single instructions (a wavefront alone on its SIMD):
+// vector and scalar instructions 4 cycles, an LDS store 22 to 34 (by its
+// width, whatever the lanes), an LDS read 8 to 15.  So words go to the other
+// lanes by lane reads and records by lane writes, not through LDS.
+// Measured, ms a sweep: 1M disks 74.4 and 65k disks 66.0, against 84.7 and 72.8
+// with what the winner has to tell sent through LDS and reflections left to the
+// general path, and about 97 and 84 with the loop compiled from C++.
+#define EC_W(x) x "\n\t"
+// g = sqrt(x), correctly rounded, as sqrt_contact; h, r scratch
+#define EC_SQRT(x, g, h, r)                                                                    \
+  EC_W("v_rsq_f64_e32 " h ", " x) EC_W("s_nop 0")                                              \
+  EC_W("v_mul_f64 " g ", " x ", " h) EC_W("v_mul_f64 " h ", " h ", 0.5")                       \
+  EC_W("v_fma_f64 " r ", -" h ", " g ", 0.5") EC_W("v_fmac_f64_e32 " g ", " g ", " r)          \
+  EC_W("v_fmac_f64_e32 " h ", " h ", " r) EC_W("v_fma_f64 " r ", -" g ", " g ", " x)           \
+  EC_W("v_fmac_f64_e32 " g ", " r ", " h) EC_W("v_fma_f64 " r ", -" g ", " g ", " x)           \
+  EC_W("v_fmac_f64_e32 " g ", " r ", " h)
+// (qx, qy) = (x, y) / d, as div_pair; r, e scratch (qy may be x)
+#define EC_DIV_PAIR(x, y, d, qx, qy, r, e)                                                     \
+  EC_W("v_rcp_f64_e32 " r ", " d) EC_W("s_nop 0")                                              \
+  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e32 " r ", " r ", " e)          \
+  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e32 " r ", " r ", " e)          \
+  EC_W("v_mul_f64 " qx ", " x ", " r) EC_W("v_fma_f64 " e ", -" d ", " qx ", " x)              \
+  EC_W("v_fmac_f64_e32 " qx ", " e ", " r)                                                     \
+  EC_W("v_mul_f64 " qy ", " y ", " r) EC_W("v_fma_f64 " e ", -" d ", " qy ", " y)              \
+  EC_W("v_fmac_f64_e32 " qy ", " e ", " r)
+// window of the mover in slot a_slot (rows clamped to the grid): its reads
+#define EC_READ_WINDOW                                                                         \
+  EC_W("s_mul_hi_u32 %[t], %[a_slot], %[inv_g32]")                                             \
+  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
+  EC_W("s_add_i32 %[u], %[t], %[offy]")                                                        \
+  EC_W("s_min_i32 %[u], %[u], %[top]")                                                         \
+  EC_W("s_max_i32 %[u], %[u], -2")                                                             \
+  EC_W("s_sub_i32 %[u], %[u], %[t]")                                                           \
+  EC_W("s_mul_i32 %[u], %[u], %[gridb]")                                                       \
+  EC_W("s_add_i32 %[u], %[u], %[a_slot]")                                                      \
+  EC_W("v_add_u32_e32 v69, %[u], %[woff]")                                                     \
+  EC_W("v_lshl_add_u32 v125, v69, 4, %[pos]")                                                  \
+  EC_W("v_lshl_add_u32 v126, v69, 2, %[meta]")                                                 \
+  EC_W("ds_read_b128 v[64:67], v125")                                                          \
+  EC_W("ds_read_b32 v98, v126")                                                                \
+  EC_W("v_lshl_add_u32 v125, %[a_slot], 4, %[pos]")                                            \
+  EC_W("ds_read_b128 v[70:73], v125")
+// the moved centre changes bin, to one that is empty (a bin holds one centre):
+// the old slot is emptied, and the disk's meta word and slot index move
+#define EC_CHANGE_BIN                                                                          \
+  EC_W("v_mov_b32_e32 v116, 0")                                                                \
+  EC_W("v_mov_b32_e32 v117, 0x7ff80000")                                                       \
+  EC_W("v_mov_b32_e32 v118, 0")                                                                \
+  EC_W("v_mov_b32_e32 v119, 0x7ff80000")                                                       \
+  EC_W("v_lshl_add_u32 v125, %[a_slot], 4, %[pos]")                                            \
+  EC_W("ds_write_b128 v125, v[116:119]")                                                       \
+  EC_W("v_lshl_add_u32 v125, v123, 2, %[meta]")                                                \
+  EC_W("v_mov_b32_e32 v126, %[a_lidx]")                                                        \
+  EC_W("ds_write_b32 v125, v126")                                                              \
+  EC_W("v_lshl_add_u32 v125, %[a_lidx], 1, %[own_loc]")                                        \
+  EC_W("ds_write_b16 v125, v123")
+// one event; K numbers its labels, BACK goes on to the next event
+#define EC_EVENT(K, LOG, STEP, BACK)                                                   \
+  EC_W("s_waitcnt lgkmcnt(0)")                                                                 \
+  /* contact distance */                                                                       \
+  EC_W("v_add_f64 v[108:109], v[66:67], -v[72:73]")                                            \
+  EC_W("v_add_f64 v[110:111], v[64:65], -v[70:71]")                                            \
+  EC_W("v_mul_f64 v[112:113], v[108:109], -v[80:81]")                                          \
+  EC_W("v_mul_f64 v[114:115], v[82:83], v[108:109]")                                           \
+  EC_W("v_fmac_f64_e32 v[112:113], v[110:111], v[82:83]")                                      \
+  EC_W("v_fmac_f64_e32 v[114:115], v[110:111], v[80:81]")                                      \
+  EC_W("v_fma_f64 v[116:117], -v[112:113], v[112:113], %[sig2]")                               \
+  EC_W("v_rsq_f64_e32 v[118:119], v[116:117]")                                                 \
+  EC_W("v_add_f64 v[78:79], v[78:79], s[92:93]")                                               \
+  EC_W("v_min_f64 v[112:113], v[114:115], v[116:117]")                                         \
+  EC_W("v_mul_f64 v[108:109], v[116:117], v[118:119]")                                         \
+  EC_W("v_mul_f64 v[118:119], v[118:119], 0.5")                                                \
+  EC_W("v_cmp_lt_f64_e32 vcc, 0, v[112:113]")                                                  \
+  EC_W("v_fma_f64 v[110:111], -v[118:119], v[108:109], 0.5")                                   \
+  EC_W("v_fmac_f64_e32 v[108:109], v[108:109], v[110:111]")                                    \
+  EC_W("v_fmac_f64_e32 v[118:119], v[118:119], v[110:111]")                                    \
+  EC_W("v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]")                            \
+  EC_W("v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]")                                    \
+  EC_W("v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]")                            \
+  EC_W("v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]")                                    \
+  EC_W("v_add_f64 v[96:97], v[114:115], -v[108:109]")                                          \
+  EC_W("v_max_f64 v[96:97], v[96:97], 0")                                                      \
+  EC_W("v_cndmask_b32_e32 v120, -1, v97, vcc")                                                 \
+  /* moved centre, its slot, tests, wave minimum */                                            \
+  EC_W("v_fma_f64 v[104:105], v[96:97], v[80:81], v[70:71]")                                   \
+  EC_W("v_fma_f64 v[106:107], v[96:97], v[82:83], v[72:73]")                                   \
+  EC_W("v_min_u32_dpp v121, v120, v120 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")        \
+  EC_W("v_add_f64 v[108:109], v[104:105], -%[mid]")                                            \
+  EC_W("v_add_f64 v[110:111], v[106:107], -%[mid]")                                            \
+  EC_W("v_min_u32_dpp v121, v121, v121 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")        \
+  EC_W("v_max_f64 v[108:109], |v[108:109]|, |v[110:111]|")                                     \
+  EC_W("v_mul_f64 v[112:113], v[106:107], %[inv_b]")                                           \
+  EC_W("v_min_u32_dpp v121, v121, v121 row_half_mirror row_mask:0xf bank_mask:0xf")            \
+  EC_W("v_mul_f64 v[114:115], v[104:105], %[inv_b]")                                           \
+  EC_W("v_cvt_i32_f64_e32 v112, v[112:113]")                                                   \
+  EC_W("v_min_u32_dpp v121, v121, v121 row_mirror row_mask:0xf bank_mask:0xf")                 \
+  EC_W("v_cvt_i32_f64_e32 v114, v[114:115]")                                                   \
+  EC_W("v_add_f64 v[108:109], v[108:109], -%[inner]")                                          \
+  EC_W("v_min_u32_dpp v121, v121, v121 row_bcast:15 row_mask:0xa bank_mask:0xf")               \
+  EC_W("v_mad_u32_u24 v123, v112, %[gridb], v114")                                             \
+  EC_W("v_add_f64 v[100:101], v[96:97], s[90:91]")                                             \
+  EC_W("v_min_u32_dpp v121, v121, v121 row_bcast:31 row_mask:0xc bank_mask:0xf")               \
+  EC_W("v_add_f64 v[110:111], v[96:97], -v[84:85]")                                            \
+  EC_W("v_and_b32_e32 v122, v101, v109")                                                       \
+  EC_W("v_readlane_b32 %[kmin], v121, 63")                                                     \
+  EC_W("v_bitop3_b32 v122, v122, v111, v98 bitop3:0x40") /* a & b & ~c */                      \
+  EC_W("v_bfi_b32 v122, %[low31], v123, v122")                                                 \
+  EC_W("v_cmp_eq_u32_e64 %[mask], %[kmin], v120")                                              \
+  /* the contact term */                                                                       \
+  EC_W("v_add_f64 v[112:113], v[64:65], -v[104:105]")                                          \
+  EC_W("v_add_f64 v[114:115], v[66:67], -v[106:107]")                                          \
+  EC_W("v_mul_f64 v[102:103], v[82:83], v[114:115]")                                           \
+  EC_W("v_fmac_f64_e32 v[102:103], v[112:113], v[80:81]")                                      \
+  EC_W("v_lshl_add_u32 v124, v123, 4, %[pos]")                                                 \
+  /* from here the winner alone: one lane, and its code is "plain, same slot" */               \
+  EC_W("s_mov_b64 exec, %[mask]")                                                              \
+  EC_W("v_readfirstlane_b32 %[t], v122")                                                       \
+  EC_W("s_bcnt1_i32_b64 %[u], %[mask]")                                                        \
+  EC_W("v_readfirstlane_b32 %[slo], v96")                                                      \
+  EC_W("v_readfirstlane_b32 %[shi], v97")                                                      \
+  EC_W("v_readfirstlane_b32 s92, v102")                                                        \
+  EC_W("v_readfirstlane_b32 s93, v103")                                                        \
+  EC_W("s_add_i32 %[u], %[u], -1")                                                             \
+  EC_W("s_xor_b32 %[t], %[t], %[expect]")                                                      \
+  EC_W("s_or_b32 %[u], %[u], %[t]")                                                            \
+  EC_W("s_cbranch_scc1 3" K "f")                                                               \
+  EC_W("4" K ":")                                                                              \
+  EC_W("v_readfirstlane_b32 %[next], v69")                                                     \
+  EC_W("ds_write_b128 v124, v[104:107]")                                                       \
+  EC_W("v_readfirstlane_b32 s90, v100")                                                        \
+  EC_W("v_readfirstlane_b32 s91, v101")                                                        \
+  EC_W("v_readfirstlane_b32 %[a_lidx], v98")                                                   \
+  LOG                                                                                          \
+  EC_W("s_mov_b32 %[a_slot], %[next]")                                                         \
+  EC_W("s_mov_b64 exec, -1")                                                                   \
+  STEP                                                                                         \
+  EC_READ_WINDOW                                                                               \
+  /* (the disk of a lift is not frozen: its meta word is its own index) */                     \
+  EC_W("v_writelane_b32 v94, %[slo], m0")                                                      \
+  EC_W("v_writelane_b32 v95, %[shi], m0")                                                      \
+  EC_W("v_writelane_b32 v99, %[a_lidx], m0")                                                   \
+  EC_W("s_add_i32 m0, m0, 1")                                                                  \
+  EC_W("s_cmp_eq_u32 m0, %[limit]")                                                            \
+  BACK
+// beside the loop: ties, bin changes, reflections
+#define EC_ASIDE(K, FROZEN)                                                                    \
+  EC_W("3" K ":")                                                                              \
+  EC_W("s_bcnt1_i32_b64 %[u], %[mask]")                                                        \
+  EC_W("s_xor_b32 %[t], %[t], %[expect]")                                                      \
+  EC_W("s_cmp_lg_u32 %[u], 1")                                                                 \
+  EC_W("s_cbranch_scc1 2f")                                                                    \
+  EC_W("s_cmp_ge_i32 %[t], 0")                                                                 \
+  EC_W("s_cbranch_scc1 " FROZEN)                                                               \
+  EC_CHANGE_BIN                                                                                \
+  EC_W("s_branch 4" K "b")
+#define EC_REFLECTION                                                                          \
+  EC_W("6:")                                                                                   \
+  /* plain but for the frozen bit? */                                                          \
+  EC_W("v_bitop3_b32 v122, v101, v109, v111 bitop3:0x80") /* a & b & c */                      \
+  EC_W("v_and_b32_e32 v122, v122, v98")                                                        \
+  EC_W("s_nop 0")                                                                              \
+  EC_W("v_readfirstlane_b32 %[t], v122")                                                       \
+  EC_W("v_readfirstlane_b32 %[next], v123")                                                    \
+  EC_W("s_cmp_ge_i32 %[t], 0")                                                                 \
+  EC_W("s_cbranch_scc1 2f")                                                                    \
+  EC_W("v_readfirstlane_b32 s90, v100")                                                        \
+  EC_W("v_readfirstlane_b32 s91, v101")                                                        \
+  /* the normal n = r / |r| of r (v112, v114) */                                               \
+  EC_W("v_mul_f64 v[108:109], v[114:115], v[114:115]")                                         \
+  EC_W("v_fmac_f64_e32 v[108:109], v[112:113], v[112:113]")                                    \
+  EC_W("s_cmp_eq_u32 %[next], %[a_slot]")                                                      \
+  EC_W("s_cbranch_scc1 8f")                                                                    \
+  EC_CHANGE_BIN                                                                                \
+  EC_W("8:")                                                                                   \
+  EC_W("ds_write_b128 v124, v[104:107]")                                                       \
+  EC_SQRT("v[108:109]", "v[110:111]", "v[116:117]", "v[118:119]")                              \
+  EC_DIV_PAIR("v[112:113]", "v[114:115]", "v[110:111]", "v[108:109]", "v[112:113]",            \
+              "v[116:117]", "v[118:119]")                                                      \
+  /* u = d - 2 (d.n) n, and the new direction u / |u| */                                       \
+  EC_W("v_mul_f64 v[114:115], v[82:83], v[112:113]")                                           \
+  EC_W("v_fmac_f64_e32 v[114:115], v[80:81], v[108:109]")                                      \
+  EC_W("v_mul_f64 v[114:115], v[114:115], -2.0")                                               \
+  EC_W("v_fma_f64 v[110:111], v[114:115], v[108:109], v[80:81]")                               \
+  EC_W("v_fma_f64 v[116:117], v[114:115], v[112:113], v[82:83]")                               \
+  EC_W("v_mul_f64 v[118:119], v[116:117], v[116:117]")                                         \
+  EC_W("v_fmac_f64_e32 v[118:119], v[110:111], v[110:111]")                                    \
+  EC_SQRT("v[118:119]", "v[108:109]", "v[112:113]", "v[114:115]")                              \
+  EC_DIV_PAIR("v[110:111]", "v[116:117]", "v[108:109]", "v[118:119]", "v[110:111]",            \
+              "v[112:113]", "v[114:115]")                                                      \
+  /* the guard of the new direction, and all of it to every lane */                            \
+  EC_W("v_max_f64 v[108:109], |v[118:119]|, |v[110:111]|")                                     \
+  EC_W("v_rcp_f64_e32 v[112:113], v[108:109]")                                                 \
+  EC_W("v_readfirstlane_b32 s94, v118")                                                        \
+  EC_W("v_readfirstlane_b32 s95, v119")                                                        \
+  EC_W("v_mul_f64 v[112:113], v[112:113], %[reach]")                                           \
+  EC_W("v_readfirstlane_b32 s96, v110")                                                        \
+  EC_W("v_readfirstlane_b32 s97, v111")                                                        \
+  EC_W("v_readfirstlane_b32 s98, v112")                                                        \
+  EC_W("v_readfirstlane_b32 s99, v113")                                                        \
+  EC_W("v_readfirstlane_b32 %[t], v98")                                                        \
+  EC_W("s_mov_b64 exec, -1")                                                                   \
+  EC_W("s_ashr_i32 %[offx], s95, 31")                                                          \
+  EC_W("s_ashr_i32 %[offy], s97, 31")                                                          \
+  EC_W("s_mul_i32 %[offx], %[offx], 3")                                                        \
+  EC_W("s_mul_i32 %[offy], %[offy], 3")                                                        \
+  EC_W("s_add_i32 %[offx], %[offx], -2")                                                       \
+  EC_W("s_add_i32 %[offy], %[offy], -2")                                                       \
+  EC_W("v_mov_b64_e32 v[80:81], s[94:95]")                                                     \
+  EC_W("v_mov_b64_e32 v[82:83], s[96:97]")                                                     \
+  EC_W("v_mov_b64_e32 v[84:85], s[98:99]")                                                     \
+  EC_W("v_add_u32_e32 %[woff], %[offx], %[loff]")                                              \
+  /* its record, kind 2: (2 ^ 1) << 29 | id */                                                 \
+  EC_W("s_and_b32 %[t], %[t], 0x1fffffff")                                                     \
+  EC_W("s_or_b32 %[t], %[t], 0x60000000")                                                      \
+  EC_W("v_writelane_b32 v94, %[slo], m0")                                                      \
+  EC_W("v_writelane_b32 v95, %[shi], m0")                                                      \
+  EC_W("v_writelane_b32 v99, %[t], m0")                                                        \
+  EC_W("s_add_i32 %[n_frozen], %[n_frozen], 1")                                                \
+  /* the same disk goes on */                                                                  \
+  EC_W("s_mov_b32 %[a_slot], %[next]")                                                         \
+  EC_READ_WINDOW                                                                               \
+  EC_W("s_add_i32 m0, m0, 1")                                                                  \
+  EC_W("s_cmp_lg_u32 m0, %[limit]")                                                            \
+  EC_W("s_cbranch_scc1 1b")                                                                    \
+  EC_W("s_branch 5f")
+// A second copy of the event saves every other taken branch.
+#define EC_LOOP(LOG, STEP, FROZEN, REFLECTION, UNDO)                                           \
   asm volatile(                                                                                \
-      "s_nop 4\n\t"                                                                            \
-      "1:\n\t"                                                                                 \
-      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
-      /* contact distance */                                                                   \
-      "v_add_f64 v[108:109], v[66:67], -v[72:73]\n\t"                                          \
-      "v_add_f64 v[110:111], v[64:65], -v[70:71]\n\t"                                          \
-      "v_mul_f64 v[112:113], v[108:109], -v[80:81]\n\t"                                        \
-      "v_mul_f64 v[114:115], v[82:83], v[108:109]\n\t"                                         \
-      "v_fmac_f64_e32 v[112:113], v[110:111], v[82:83]\n\t"                                    \
-      "v_fmac_f64_e32 v[114:115], v[110:111], v[80:81]\n\t"                                    \
-      "v_fma_f64 v[116:117], -v[112:113], v[112:113], %[sig2]\n\t"                             \
-      "v_rsq_f64_e32 v[118:119], v[116:117]\n\t"                                               \
-      "v_add_f64 v[78:79], v[78:79], v[76:77]\n\t"                                             \
-      "v_min_f64 v[112:113], v[114:115], v[116:117]\n\t"                                       \
-      "v_mul_f64 v[108:109], v[116:117], v[118:119]\n\t"                                       \
-      "v_mul_f64 v[118:119], v[118:119], 0.5\n\t"                                              \
-      "v_cmp_lt_f64_e32 vcc, 0, v[112:113]\n\t"                                                \
-      "v_fma_f64 v[110:111], -v[118:119], v[108:109], 0.5\n\t"                                 \
-      "v_fmac_f64_e32 v[108:109], v[108:109], v[110:111]\n\t"                                  \
-      "v_fmac_f64_e32 v[118:119], v[118:119], v[110:111]\n\t"                                  \
-      "v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]\n\t"                          \
-      "v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]\n\t"                                  \
-      "v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]\n\t"                          \
-      "v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]\n\t"                                  \
-      "v_add_f64 v[96:97], v[114:115], -v[108:109]\n\t"                                        \
-      "v_max_f64 v[96:97], v[96:97], 0\n\t"                                                    \
-      "v_cndmask_b32_e32 v120, -1, v97, vcc\n\t"                                               \
-      /* moved centre, tests and wave minimum */                                               \
-      "v_fma_f64 v[104:105], v[96:97], v[80:81], v[70:71]\n\t"                                 \
-      "v_fma_f64 v[106:107], v[96:97], v[82:83], v[72:73]\n\t"                                 \
-      "v_min_u32_dpp v121, v120, v120 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"      \
-      "v_add_f64 v[108:109], v[104:105], -%[mid]\n\t"                                          \
-      "v_add_f64 v[110:111], v[106:107], -%[mid]\n\t"                                          \
-      "v_min_u32_dpp v121, v121, v121 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"      \
-      "v_max_f64 v[108:109], |v[108:109]|, |v[110:111]|\n\t"                                   \
-      "v_mul_f64 v[112:113], v[106:107], %[inv_b]\n\t"                                         \
-      "v_min_u32_dpp v121, v121, v121 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"          \
-      "v_mul_f64 v[114:115], v[104:105], %[inv_b]\n\t"                                         \
-      "v_cvt_i32_f64_e32 v112, v[112:113]\n\t"                                                 \
-      "v_min_u32_dpp v121, v121, v121 row_mirror row_mask:0xf bank_mask:0xf\n\t"               \
-      "v_cvt_i32_f64_e32 v114, v[114:115]\n\t"                                                 \
-      "v_add_f64 v[108:109], v[108:109], -%[inner]\n\t"                                        \
-      "v_min_u32_dpp v121, v121, v121 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"             \
-      "v_mad_u32_u24 v123, v112, %[gridb], v114\n\t"                                           \
-      "v_add_f64 v[100:101], v[96:97], v[74:75]\n\t"                                           \
-      "v_min_u32_dpp v121, v121, v121 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"             \
-      "v_add_f64 v[110:111], v[96:97], -v[84:85]\n\t"                                          \
-      "v_and_b32_e32 v122, v101, v109\n\t"                                                     \
-      "v_readlane_b32 %[kmin], v121, 63\n\t"                                                   \
-      "v_bitop3_b32 v122, v122, v111, v98 bitop3:0x40\n\t" /* a & b & ~c */                    \
-      "v_bfi_b32 v122, %[low31], v123, v122\n\t"                                               \
-      "v_cmp_eq_u32_e64 %[mask], %[kmin], v120\n\t"                                            \
-      "v_add_f64 v[108:109], v[64:65], -v[104:105]\n\t"                                        \
-      "v_add_f64 v[110:111], v[66:67], -v[106:107]\n\t"                                        \
-      "v_mul_f64 v[102:103], v[82:83], v[110:111]\n\t"                                         \
-      "v_fmac_f64_e32 v[102:103], v[108:109], v[80:81]\n\t"                                    \
-      "v_lshl_add_u32 v124, v123, 4, %[pos]\n\t"                                               \
-      /* from here the winner alone */                                                         \
-      "s_mov_b64 exec, %[mask]\n\t"                                                            \
-      "v_readfirstlane_b32 %[t], v122\n\t"                                                     \
-      "v_readfirstlane_b32 %[slot], v69\n\t"                                                   \
-      "s_bcnt1_i32_b64 %[u], %[mask]\n\t"                                                      \
-      "ds_write_b96 v94, v[96:98]\n\t"                                                         \
-      "ds_write_b128 %[mail], v[100:103]\n\t"                                                  \
-      "s_cmp_lg_u32 %[u], 1\n\t"                                                               \
-      "s_cbranch_scc1 2f\n\t"                                                                  \
-      "s_xor_b32 %[u], %[t], %[a_slot]\n\t"                                                    \
-      "s_cmp_lg_u32 %[u], 0x80000000\n\t"                                                      \
-      "s_cbranch_scc1 3f\n\t"                                                                  \
-      "4:\n\t"                                                                                 \
-      "ds_write_b128 v124, v[104:107]\n\t"                                                     \
-      "v_readfirstlane_b32 %[a_lidx], v98\n\t"                                                 \
-      LOG                                                                                      \
-      "s_mov_b64 exec, -1\n\t"                                                                 \
-      STEP                                                                                     \
-      /* the next window: rows clamped to the grid */                                          \
-      "s_mov_b32 %[a_slot], %[slot]\n\t"                                                       \
-      "s_mul_i32 %[t], %[slot], %[inv_g20]\n\t"                                                \
-      "s_lshr_b32 %[t], %[t], 20\n\t"                                                          \
-      "s_add_i32 %[u], %[t], %[offy]\n\t"                                                      \
-      "s_min_i32 %[u], %[u], %[top]\n\t"                                                       \
-      "s_max_i32 %[u], %[u], -2\n\t"                                                           \
-      "s_sub_i32 %[u], %[u], %[t]\n\t"                                                         \
-      "s_mul_i32 %[u], %[u], %[gridb]\n\t"                                                     \
-      "s_add_i32 %[u], %[u], %[slot]\n\t"                                                      \
-      "v_add_u32_e32 v69, %[u], %[woff]\n\t"                                                   \
-      "v_lshl_add_u32 v125, v69, 4, %[pos]\n\t"                                                \
-      "v_lshl_add_u32 v126, v69, 2, %[meta]\n\t"                                               \
-      "ds_read_b128 v[64:67], v125\n\t"                                                        \
-      "ds_read_b32 v98, v126\n\t"                                                              \
-      "v_lshl_add_u32 v125, %[slot], 4, %[pos]\n\t"                                            \
-      "ds_read_b128 v[70:73], v125\n\t"                                                        \
-      "ds_read_b128 v[74:77], %[mail]\n\t"                                                     \
-      "v_add_u32_e32 v94, 16, v94\n\t"                                                         \
-      "s_add_i32 %[n_ring], %[n_ring], 1\n\t"                                                  \
-      "s_cmp_lg_u32 %[n_ring], %[limit]\n\t"                                                   \
-      "s_cbranch_scc1 1b\n\t"                                                                  \
-      "s_mov_b32 %[full], 1\n\t"                                                               \
-      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
-      "v_add_f64 v[78:79], v[78:79], v[76:77]\n\t"                                             \
-      "s_branch 5f\n\t"                                                                        \
-      /* not plain, or the moved centre is in another bin, which is empty (a bin holds one */  \
-      /* centre): the old slot is emptied, and the disk's meta word and slot index move    */  \
-      "3:\n\t"                                                                                 \
-      "s_cmp_ge_i32 %[t], 0\n\t"                                                               \
-      "s_cbranch_scc1 2f\n\t"                                                                  \
-      "v_mov_b32_e32 v108, 0\n\t"                                                              \
-      "v_mov_b32_e32 v109, 0x7ff80000\n\t"                                                     \
-      "v_mov_b32_e32 v110, 0\n\t"                                                              \
-      "v_mov_b32_e32 v111, 0x7ff80000\n\t"                                                     \
-      "v_lshl_add_u32 v125, %[a_slot], 4, %[pos]\n\t"                                          \
-      "ds_write_b128 v125, v[108:111]\n\t"                                                     \
-      "v_lshl_add_u32 v125, v123, 2, %[meta]\n\t"                                              \
-      "v_mov_b32_e32 v126, %[a_lidx]\n\t"                                                      \
-      "ds_write_b32 v125, v126\n\t"                                                            \
-      "v_lshl_add_u32 v125, %[a_lidx], 1, %[own_loc]\n\t"                                      \
-      "ds_write_b16 v125, v123\n\t"                                                            \
-      "s_branch 4b\n\t"                                                                        \
-      "2:\n\t"                                                                                 \
-      "s_mov_b64 exec, -1\n\t"                                                                 \
-      "s_mov_b32 %[full], 0\n\t"                                                               \
-      "s_waitcnt lgkmcnt(0)\n\t"                                                               \
-      "5:\n\t"                                                                                 \
+      EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                        \
+      EC_W("s_nop 3")                                                                          \
+      EC_W("1:")                                                                               \
+      EC_EVENT("1", LOG, STEP, EC_W("s_cbranch_scc1 5f"))                                      \
+      EC_EVENT("2", LOG, STEP, EC_W("s_cbranch_scc0 1b"))                                      \
+      EC_W("s_branch 5f")                                                                      \
+      EC_ASIDE("1", FROZEN)                                                                    \
+      EC_ASIDE("2", FROZEN)                                                                    \
+      REFLECTION                                                                               \
+      EC_W("5:")                                                                               \
+      EC_W("s_mov_b32 %[full], 1")                                                             \
+      EC_W("s_waitcnt lgkmcnt(0)")                                                             \
+      EC_W("v_add_f64 v[78:79], v[78:79], s[92:93]")                                           \
+      EC_W("s_branch 9f")                                                                      \
+      EC_W("2:")                                                                               \
+      EC_W("s_mov_b64 exec, -1")                                                               \
+      EC_W("s_mov_b32 %[full], 0")                                                             \
+      EC_W("s_waitcnt lgkmcnt(0)")                                                             \
+      EC_W("9:")                                                                               \
       "s_nop 4"                                                                                \
       : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(widx), "+{v[70:71]}"(ax),             \
-        "+{v[72:73]}"(ay), "+{v[74:75]}"(nrem), "+{v[76:77]}"(dacc), "+{v[78:79]}"(sum),       \
-        "+{v94}"(rec_at), "+{v98}"(m), "={v[96:97]}"(s), "={v120}"(key),                       \
+        "+{v[72:73]}"(ay), "+{s[90:91]}"(nrem), "+{s[92:93]}"(dacc), "+{v[78:79]}"(sum),       \
+        "+{v[80:81]}"(dx), "+{v[82:83]}"(dy), "+{v[84:85]}"(guard), "+{v94}"(rec_lo),          \
+        "+{v95}"(rec_hi), "+{v98}"(m), "+{v99}"(rec_tag), "={v[96:97]}"(s), "={v120}"(key),    \
         [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+s"(a_slot),                      \
-        [a_lidx] "+s"(a_lidx), [n_ring] "+s"(n_ring), [mask] "=&s"(a_mask), [t] "=&s"(a_t),    \
-        [u] "=&s"(a_u), [slot] "=&s"(a_next) UNDO                                              \
-      : "{v[80:81]}"(dx), "{v[82:83]}"(dy), "{v[84:85]}"(guard), [pos] "v"(pos_at),            \
-        [meta] "v"(meta_at), [own_loc] "v"(own_loc_at), [mail] "v"(mail_at),                   \
-        [woff] "v"(loff + offx), [mid] "s"(mid), [inner] "s"(inner), [sig2] "s"(s_sig2),       \
-        [inv_b] "s"(s_inv_b), [gridb] "s"(s_gridb), [inv_g20] "s"(s_inv_g20),                  \
-        [offy] "s"(uniform_i32(offy)), [top] "s"(s_top), [limit] "s"(uniform_i32(limit)),      \
-        [low31] "s"(0x7FFFFFFF)                                                                \
-      : "vcc", "scc", "memory", "v100", "v101", "v102", "v103", "v104", "v105", "v106",        \
-        "v107", "v108", "v109", "v110", "v111", "v112", "v113", "v114", "v115", "v116",        \
-        "v117", "v118", "v119", "v121", "v122", "v123", "v124", "v125", "v126", "v127")
+        [a_lidx] "+s"(a_lidx), "+{m0}"(n_ring), [offx] "+s"(offx), [offy] "+s"(offy),    \
+        [n_frozen] "+s"(n_frozen), [woff] "+v"(woff), [mask] "=&s"(a_mask), [t] "=&s"(a_t),    \
+        [u] "=&s"(a_u), [next] "=&s"(a_next), [slo] "=&s"(a_slo), [shi] "=&s"(a_shi),          \
+        [expect] "=&s"(a_expect) UNDO                                                          \
+      : [pos] "v"(pos_at), [meta] "v"(meta_at), [own_loc] "v"(own_loc_at), [loff] "v"(loff),   \
+        [mid] "s"(mid), [inner] "s"(inner), [sig2] "s"(s_sig2), [inv_b] "s"(s_inv_b),          \
+        [reach] "s"(s_reach), [gridb] "s"(s_gridb), [inv_g32] "s"(s_inv_g32),                  \
+        [top] "s"(s_top), [limit] "s"(limit), [low31] "s"(0x7FFFFFFF)                          \
+      : "vcc", "scc", "memory", "s94", "s95", "s96", "s97", "s98", "s99", "v100",        \
+        "v101", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v109", "v110",        \
+        "v111", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v121",        \
+        "v122", "v123", "v124", "v125", "v126", "v127")
 // The rejection variant's undo log of a plain lift: slots before and after, old
 // position; then the next entry's addresses.
 #define EC_UNDO_LOG                                                                            \
-  "v_mov_b32_e32 v126, %[a_slot]\n\t"                                                          \
-  "v_mov_b32_e32 v127, v123\n\t"                                                               \
-  "ds_write_b64 %[uslot], v[126:127]\n\t"                                                      \
-  "ds_write_b128 %[upos], v[70:73]\n\t"
+  EC_W("v_mov_b32_e32 v126, %[a_slot]")                                                        \
+  EC_W("v_mov_b32_e32 v127, v123")                                                             \
+  EC_W("ds_write_b64 %[uslot], v[126:127]")                                                    \
+  EC_W("ds_write_b128 %[upos], v[70:73]")
 #define EC_UNDO_STEP                                                                           \
-  "v_add_u32_e32 %[uslot], 8, %[uslot]\n\t"                                                    \
-  "v_add_u32_e32 %[upos], 16, %[upos]\n\t"
+  EC_W("v_add_u32_e32 %[uslot], 8, %[uslot]")                                                  \
+  EC_W("v_add_u32_e32 %[upos], 16, %[upos]")
 #define EC_UNDO_OPERANDS , [uslot] "+v"(uslot_at), [upos] "+v"(upos_at)
 
 // Both components of (x, y) / den: the compiler's own FP64 division sequence
@@ -971,10 +1093,9 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // Slots are counted from that of the first own bin (bin (0, 0) of nb x nb;
   // the frozen band's bins are -2, -1, nb and nb + 1): slot = by * gridb + bx.
   const int qoff = 2 * gridb + 2;
-  // row of an own slot: floor(slot / gridb) as (slot * m) >> 20 with m =
-  // ceil(2^20 / gridb), exact for 0 <= slot < gridb^2 when gridb^3 < 2^20 (the
-  // host limits gridb to 100)
-  const uint32_t inv_g20 = ((1u << 20) + (uint32_t)gridb - 1u) / (uint32_t)gridb;
+  // row of an own slot: floor(slot / gridb) as (slot * m) >> 32 with m =
+  // ceil(2^32 / gridb), exact for 0 <= slot < gridb^2 <= 100^2
+  const uint32_t inv_g32 = 0xFFFFFFFFu / (uint32_t)gridb + 1u;
 
   const CellLds lay = cell_lds_layout(gridb, d.cap_own, REJ == 1);
   double2* const pos_all = (double2*)(base + lay.off_pos);
@@ -986,7 +1107,6 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // the id staging buffer of the rank sort lies in the position slots, which
   // are filled only after the sort
   int32_t* tmp = (int32_t*)(base + lay.off_pos);
-  uint32_t* const rec = (uint32_t*)(base + lay.off_rec);  // event records of the digest
   // REJ 1 only: per logged lift the old position, then (slot before, slot after)
   double2* undo_pos = (double2*)(base + lay.off_undo);
   int2* undo_slot = (int2*)(undo_pos + kUndoCap);
@@ -1083,11 +1203,11 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   double acc = d.acc_delta[cell];
   uint32_t n_lift = 0, n_frozen = 0, n_wall = 0;
   uint64_t h = 0;
-  int n_ring = 0;            // event records held
+  int n_ring = 0;            // event records held in the lanes (lane k: record k)
   uint64_t ring_first = 0;    // digest index of record 0
+  uint32_t rec_lo = 0, rec_hi = 0, rec_tag = 0;
   // LDS addresses of the plain-lift loop
-  const uint32_t pos_at = lds_address(pos), meta_at = lds_address(meta), own_loc_at = lds_address(own_loc),
-                 mail_at = lds_address(base + lay.off_mail), rec_base = lds_address(rec);
+  const uint32_t pos_at = lds_address(pos), meta_at = lds_address(meta), own_loc_at = lds_address(own_loc);
   // lane = lx + 8 ly: one bin of an 8 x 8 window per lane, a window row in 8
   // neighbouring lanes
   const int loff = (lane >> 3) * gridb + (lane & 7);  // this lane's slot inside a window
@@ -1109,7 +1229,8 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // (the loop's scalar operands, read as such)
   const double mid = readlane_f64(0.5 * w, 0), inner = readlane_f64(0.5 * w - eps, 0);
   const double s_sig2 = readlane_f64(sig2, 0), s_inv_b = readlane_f64(inv_b, 0);
-  const int s_gridb = uniform_i32(gridb), s_inv_g20 = uniform_i32((int)inv_g20), s_top = uniform_i32(nb - 6);
+  const double s_reach = readlane_f64(reach * (1.0 - 0x1p-20), 0);
+  const int s_gridb = uniform_i32(gridb), s_inv_g32 = uniform_i32((int)inv_g32), s_top = uniform_i32(nb - 6);
   const bool use_window = d.search == 0;
   const uint64_t wall_x_id = (uint64_t)d.n, wall_y_id = (uint64_t)d.n + 1, end_id = (uint64_t)d.n + 3;
   int aborted = 0;
@@ -1138,7 +1259,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 #define EC_SET_DIRECTION()                                                          \
     do {                                                                            \
       const double lead_ = fmax(fabs(dx), fabs(dy));                                \
-      dsafe = use_window ? (reach * (1.0 - 0x1p-20)) * __builtin_amdgcn_rcp(lead_) : -1.0; \
+      dsafe = use_window ? s_reach * __builtin_amdgcn_rcp(lead_) : -1.0;            \
       offx = uniform_i32(dx < 0.0 ? -5 : -2);                                       \
       offy = uniform_i32(dy < 0.0 ? -5 : -2);                                       \
     } while (0)
@@ -1146,7 +1267,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
     // position and meta word, and the mover's position
 #define EC_WINDOW()                                                                 \
     do {                                                                            \
-      const int by_ = (int)(((uint32_t)a_slot * inv_g20) >> 20);                    \
+      const int by_ = (int)__umulhi((uint32_t)a_slot, inv_g32);                     \
       const int wy_ = max(min(by_ + offy, nb - 6), -2);                             \
       widx = (a_slot + offx + (wy_ - by_) * gridb) + loff;                          \
       p = pos[widx];                                                                \
@@ -1176,7 +1297,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 #define EC_FLUSH()                                                                  \
     do {                                                                            \
       uint32_t lifts_;                                                              \
-      h ^= digest_records(rec, lane, kDigestBatch, ring_first, own_gid, lifts_);    \
+      h ^= digest_records(rec_lo, rec_hi, rec_tag, lane, kDigestBatch, ring_first, own_gid, lifts_); \
       if (REJ == 0) n_lift += lifts_;                                               \
       ring_first += kDigestBatch;                                                   \
       n_ring = 0;                                                                   \
@@ -1197,28 +1318,33 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       // (all ones: no contact) and the wave minimum of those
       double s;
       uint32_t key, key_min;
-      // plain lifts, up to the next digest of 64 records
+      // plain lifts and reflections, up to the next digest of 64 records
       for (;;) {
         const int before = n_ring;
-        double sum = REJ == 1 ? chain_acc : acc, dacc = 0.0, guard = dsafe;
-        int limit = kDigestBatch, full, a_t, a_u, a_next;
+        double sum = REJ == 1 ? chain_acc : acc, dacc = 0.0;
+        int limit = kDigestBatch, full, a_t, a_u, a_next, a_slo, a_shi, a_expect, woff = loff + offx;
         uint64_t a_mask;
-        uint32_t rec_at = rec_base + (uint32_t)(kRecSlot * n_ring);
+        nrem = readlane_f64(nrem, 0);
         a_slot = uniform_i32(a_slot);
         a_lidx = uniform_i32(a_lidx);
         n_ring = uniform_i32(n_ring);
+        n_frozen = (uint32_t)uniform_i32((int)n_frozen);
+        offx = uniform_i32(offx);
+        offy = uniform_i32(offy);
         if (REJ == 1) {
           // the log's end is a limit too; with a full log no lift is plain
           // (whose move would be the general path's error)
-          if (n_undo == kUndoCap) guard = -1.0;
-          else limit = min(limit, n_ring + kUndoCap - n_undo);
+          double guard = n_undo == kUndoCap ? -1.0 : dsafe;
+          if (n_undo < kUndoCap) limit = min(limit, n_ring + kUndoCap - n_undo);
+          limit = uniform_i32(limit);
           uint32_t upos_at = lds_address(undo_pos + n_undo), uslot_at = lds_address(undo_slot + n_undo);
-          EC_PLAIN_LOOP(EC_UNDO_LOG, EC_UNDO_STEP, EC_UNDO_OPERANDS);
+          EC_LOOP(EC_UNDO_LOG, EC_UNDO_STEP, "2f", "", EC_UNDO_OPERANDS);
           chain_acc = sum;
           n_undo += n_ring - before;
           chain_lifts += (uint32_t)(n_ring - before);
         } else {
-          EC_PLAIN_LOOP("", "", );
+          double& guard = dsafe;
+          EC_LOOP("", "", "6f", EC_REFLECTION, );
           acc = sum;
         }
         if (full == 0) break;
@@ -1317,14 +1443,14 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       // REJ 1: a wall or a frozen disk rejects the chain
       const bool rejected = REJ == 1 && kind != EV_END && kind != EV_LIFT;
       {
-        // event record for the digest (all lanes store the same)
+        // event record for the digest, kept by lane n_ring
         const uint32_t eid = kind == EV_END ? (uint32_t)end_id
                              : (kind == EV_WALL_X ? (uint32_t)wall_x_id
                                                   : (kind == EV_WALL_Y ? (uint32_t)wall_y_id
                                                                        : (wm & ~kFrozenBit)));
         const uint64_t sb = (uint64_t)__double_as_longlong(step);
-        *(uint4*)(rec + (kRecSlot / 4) * n_ring) =
-            make_uint4((uint32_t)sb, (uint32_t)(sb >> 32), ((uint32_t)(kind ^ 1) << 29) | eid, 0u);
+        writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
+                   ((uint32_t)(kind ^ 1) << 29) | eid, n_ring);
       }
       if (REJ == 1 && kind == EV_LIFT && n_undo == kUndoCap) {
         // a full log stops the sweep with an error
@@ -1447,7 +1573,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // ---- write back: old position + local displacement, wrapped --------------
   wave_sync();
   uint32_t last_lifts;
-  h ^= digest_records(rec, lane, n_ring, ring_first, own_gid, last_lifts);
+  h ^= digest_records(rec_lo, rec_hi, rec_tag, lane, n_ring, ring_first, own_gid, last_lifts);
   if (REJ == 0) n_lift += last_lifts;
   // The cell's id list is sorted again by the regions of the moved disks:
   // the neighbours of later colour phases stage their frozen band from the
