@@ -770,7 +770,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // vector and scalar instructions 4 cycles, an LDS store 22 to 34 (by its
 // width, whatever the lanes), an LDS read 8 to 15.  So words go to the other
 // lanes by lane reads and records by lane writes, not through LDS.
-// Measured, ms a sweep: 1M disks 74.4 and 65k disks 66.0, against 84.7 and 72.8
+// Measured, ms a sweep: 1M disks 72.8 and 65k disks 64.6, against 84.7 and 72.8
 // with what the winner has to tell sent through LDS and reflections left to the
 // general path, and about 97 and 84 with the loop compiled from C++.
 #define EC_W(x) x "\n\t"
@@ -780,17 +780,17 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_mul_f64 " g ", " x ", " h) EC_W("v_mul_f64 " h ", " h ", 0.5")                       \
   EC_W("v_fma_f64 " r ", -" h ", " g ", 0.5") EC_W("v_fmac_f64_e32 " g ", " g ", " r)          \
   EC_W("v_fmac_f64_e32 " h ", " h ", " r) EC_W("v_fma_f64 " r ", -" g ", " g ", " x)           \
-  EC_W("v_fmac_f64_e32 " g ", " r ", " h) EC_W("v_fma_f64 " r ", -" g ", " g ", " x)           \
-  EC_W("v_fmac_f64_e32 " g ", " r ", " h)
+  EC_W("v_fmac_f64_e64 " g ", " r ", " h) EC_W("v_fma_f64 " r ", -" g ", " g ", " x)           \
+  EC_W("v_fmac_f64_e64 " g ", " r ", " h)
 // (qx, qy) = (x, y) / d, as div_pair; r, e scratch (qy may be x)
 #define EC_DIV_PAIR(x, y, d, qx, qy, r, e)                                                     \
   EC_W("v_rcp_f64_e32 " r ", " d) EC_W("s_nop 0")                                              \
-  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e32 " r ", " r ", " e)          \
-  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e32 " r ", " r ", " e)          \
+  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e64 " r ", " r ", " e)          \
+  EC_W("v_fma_f64 " e ", -" d ", " r ", 1.0") EC_W("v_fmac_f64_e64 " r ", " r ", " e)          \
   EC_W("v_mul_f64 " qx ", " x ", " r) EC_W("v_fma_f64 " e ", -" d ", " qx ", " x)              \
-  EC_W("v_fmac_f64_e32 " qx ", " e ", " r)                                                     \
+  EC_W("v_fmac_f64_e64 " qx ", " e ", " r)                                                     \
   EC_W("v_mul_f64 " qy ", " y ", " r) EC_W("v_fma_f64 " e ", -" d ", " qy ", " y)              \
-  EC_W("v_fmac_f64_e32 " qy ", " e ", " r)
+  EC_W("v_fmac_f64_e64 " qy ", " e ", " r)
 // window of the mover in slot a_slot (rows clamped to the grid): its reads
 #define EC_READ_WINDOW                                                                         \
   EC_W("s_mul_hi_u32 %[t], %[a_slot], %[inv_g32]")                                             \
@@ -801,7 +801,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("s_sub_i32 %[u], %[u], %[t]")                                                           \
   EC_W("s_mul_i32 %[u], %[u], %[gridb]")                                                       \
   EC_W("s_add_i32 %[u], %[u], %[a_slot]")                                                      \
-  EC_W("v_add_u32_e32 v69, %[u], %[woff]")                                                     \
+  EC_W("v_add_u32_e64 v69, %[u], %[woff]")                                                     \
   EC_W("v_lshl_add_u32 v125, v69, 4, %[pos]")                                                  \
   EC_W("v_lshl_add_u32 v126, v69, 2, %[meta]")                                                 \
   EC_W("ds_read_b128 v[64:67], v125")                                                          \
@@ -833,22 +833,22 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_fmac_f64_e32 v[112:113], v[110:111], v[82:83]")                                      \
   EC_W("v_fmac_f64_e32 v[114:115], v[110:111], v[80:81]")                                      \
   EC_W("v_fma_f64 v[116:117], -v[112:113], v[112:113], %[sig2]")                               \
-  EC_W("v_rsq_f64_e32 v[118:119], v[116:117]")                                                 \
+  EC_W("v_rsq_f64_e64 v[118:119], v[116:117]")                                                 \
   EC_W("v_add_f64 v[78:79], v[78:79], s[92:93]")                                               \
   EC_W("v_min_f64 v[112:113], v[114:115], v[116:117]")                                         \
   EC_W("v_mul_f64 v[108:109], v[116:117], v[118:119]")                                         \
   EC_W("v_mul_f64 v[118:119], v[118:119], 0.5")                                                \
-  EC_W("v_cmp_lt_f64_e32 vcc, 0, v[112:113]")                                                  \
+  EC_W("v_cmp_lt_f64_e64 vcc, 0, v[112:113]")                                                  \
   EC_W("v_fma_f64 v[110:111], -v[118:119], v[108:109], 0.5")                                   \
   EC_W("v_fmac_f64_e32 v[108:109], v[108:109], v[110:111]")                                    \
   EC_W("v_fmac_f64_e32 v[118:119], v[118:119], v[110:111]")                                    \
   EC_W("v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]")                            \
-  EC_W("v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]")                                    \
+  EC_W("v_fmac_f64_e64 v[108:109], v[110:111], v[118:119]")                                    \
   EC_W("v_fma_f64 v[110:111], -v[108:109], v[108:109], v[116:117]")                            \
-  EC_W("v_fmac_f64_e32 v[108:109], v[110:111], v[118:119]")                                    \
+  EC_W("v_fmac_f64_e64 v[108:109], v[110:111], v[118:119]")                                    \
   EC_W("v_add_f64 v[96:97], v[114:115], -v[108:109]")                                          \
   EC_W("v_max_f64 v[96:97], v[96:97], 0")                                                      \
-  EC_W("v_cndmask_b32_e32 v120, -1, v97, vcc")                                                 \
+  EC_W("v_cndmask_b32_e64 v120, -1, v97, vcc")                                                 \
   /* moved centre, its slot, tests, wave minimum */                                            \
   EC_W("v_fma_f64 v[104:105], v[96:97], v[80:81], v[70:71]")                                   \
   EC_W("v_fma_f64 v[106:107], v[96:97], v[82:83], v[72:73]")                                   \
@@ -860,16 +860,16 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_mul_f64 v[112:113], v[106:107], %[inv_b]")                                           \
   EC_W("v_min_u32_dpp v121, v121, v121 row_half_mirror row_mask:0xf bank_mask:0xf")            \
   EC_W("v_mul_f64 v[114:115], v[104:105], %[inv_b]")                                           \
-  EC_W("v_cvt_i32_f64_e32 v112, v[112:113]")                                                   \
+  EC_W("v_cvt_i32_f64_e64 v112, v[112:113]")                                                   \
   EC_W("v_min_u32_dpp v121, v121, v121 row_mirror row_mask:0xf bank_mask:0xf")                 \
-  EC_W("v_cvt_i32_f64_e32 v114, v[114:115]")                                                   \
+  EC_W("v_cvt_i32_f64_e64 v114, v[114:115]")                                                   \
   EC_W("v_add_f64 v[108:109], v[108:109], -%[inner]")                                          \
   EC_W("v_min_u32_dpp v121, v121, v121 row_bcast:15 row_mask:0xa bank_mask:0xf")               \
   EC_W("v_mad_u32_u24 v123, v112, %[gridb], v114")                                             \
   EC_W("v_add_f64 v[100:101], v[96:97], s[90:91]")                                             \
   EC_W("v_min_u32_dpp v121, v121, v121 row_bcast:31 row_mask:0xc bank_mask:0xf")               \
   EC_W("v_add_f64 v[110:111], v[96:97], -v[84:85]")                                            \
-  EC_W("v_and_b32_e32 v122, v101, v109")                                                       \
+  EC_W("v_and_b32_e64 v122, v101, v109")                                                       \
   EC_W("v_readlane_b32 %[kmin], v121, 63")                                                     \
   EC_W("v_bitop3_b32 v122, v122, v111, v98 bitop3:0x40") /* a & b & ~c */                      \
   EC_W("v_bfi_b32 v122, %[low31], v123, v122")                                                 \
@@ -878,7 +878,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_add_f64 v[112:113], v[64:65], -v[104:105]")                                          \
   EC_W("v_add_f64 v[114:115], v[66:67], -v[106:107]")                                          \
   EC_W("v_mul_f64 v[102:103], v[82:83], v[114:115]")                                           \
-  EC_W("v_fmac_f64_e32 v[102:103], v[112:113], v[80:81]")                                      \
+  EC_W("v_fmac_f64_e64 v[102:103], v[112:113], v[80:81]")                                      \
   EC_W("v_lshl_add_u32 v124, v123, 4, %[pos]")                                                 \
   /* from here the winner alone: one lane, and its code is "plain, same slot" */               \
   EC_W("s_mov_b64 exec, %[mask]")                                                              \
@@ -991,11 +991,17 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("s_cmp_lg_u32 m0, %[limit]")                                                            \
   EC_W("s_cbranch_scc1 1b")                                                                    \
   EC_W("s_branch 5f")
-// A second copy of the event saves every other taken branch.
+// A second copy of the event saves every other taken branch (four are no faster).
+// The code is laid out so that no 8-byte instruction crosses an 8-byte boundary:
+// in a run of such instructions each costs a cycle more where they do.  So 4-byte
+// instructions come in pairs, single ones in their 8-byte encoding (_e64), and
+// the loop starts 4 bytes past a 32-byte boundary.
 #define EC_LOOP(LOG, STEP, FROZEN, REFLECTION, UNDO)                                           \
   asm volatile(                                                                                \
       EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                        \
       EC_W("s_nop 3")                                                                          \
+      EC_W(".p2align 5")                                                                       \
+      EC_W("s_nop 0")                                                                          \
       EC_W("1:")                                                                               \
       EC_EVENT("1", LOG, STEP, EC_W("s_cbranch_scc1 5f"))                                      \
       EC_EVENT("2", LOG, STEP, EC_W("s_cbranch_scc0 1b"))                                      \
