@@ -79,6 +79,25 @@ struct Stream {
   }
 };
 
+// Loads and stores of global memory through a record's pointers.  A pointer
+// that was itself loaded is generic to the compiler, and a generic (flat)
+// access counts as an LDS access too: every LDS wait after it also waits for
+// memory, 1 to 2 us.
+#define EC_GLOBAL(T) __attribute__((address_space(1))) T
+template <class T>
+__device__ __forceinline__ T gload(const T* p) {
+  return *(const EC_GLOBAL(T)*)p;
+}
+__device__ __forceinline__ double2 gload(const double2* p) {
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  const pair_t v = *(const EC_GLOBAL(pair_t)*)p;
+  return make_double2(v.x, v.y);
+}
+template <class T>
+__device__ __forceinline__ void gstore(T* p, T v) {
+  *(EC_GLOBAL(T)*)p = v;
+}
+
 __device__ __forceinline__ double u01(uint64_t w) { return (double)(w >> 11) * 0x1.0p-53; }
 
 // Lemire's multiply-shift with rejection: exactly uniform on [0, n).
@@ -567,7 +586,7 @@ __device__ __forceinline__ int64_t chains_of(const Dev& d, int n_c) {
   return d.chains_per_cell > 0 ? d.chains_per_cell : n_c;
 }
 __device__ __forceinline__ int64_t chain_base(const Dev& d, int cell) {
-  return d.chains_per_cell > 0 ? (int64_t)cell * d.chains_per_cell : (int64_t)d.cell_start[cell];
+  return d.chains_per_cell > 0 ? (int64_t)cell * d.chains_per_cell : (int64_t)gload(d.cell_start + cell);
 }
 
 __device__ bool draw_index_capped(Stream& st, uint64_t n, uint64_t& out) {
@@ -709,7 +728,7 @@ __device__ __forceinline__ int argmin_lane_slots(double s, uint32_t m, const int
 }
 
 __device__ __forceinline__ int32_t load_err(const Dev& d) {
-  return __hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load((const EC_GLOBAL(int32_t)*)d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------
@@ -1172,19 +1191,43 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   double2* undo_pos = (double2*)(base + lay.off_undo);
   int2* undo_slot = (int2*)(undo_pos + kUndoCap);
 
-  // ---- stage: own disks, sorted by id -----------------------------------
-  const int start = d.cell_start[cell];
-  const int n_own = d.cell_start[cell + 1] - start;
-  if (n_own < 0 || n_own > d.cap_own || start < 0 || (int64_t)start + n_own > d.n) {
+  // ---- stage ---------------------------------------------------------------
+  // Lists of disks to read, one per lane, so that their bounds come in one trip
+  // to memory: lanes 0-11 the frozen band, lane 12 the cell's own list.  The
+  // band is the centres of the 8 neighbouring cells within sigma of this cell.
+  // Only a neighbour's regions that face this cell are read (its wall strips
+  // are wider than sigma, so they hold every such centre): the strip along the
+  // shared wall of an edge neighbour, the corner region of a diagonal one.  A
+  // region row is one range of the list, a region column three.
+  int s0 = 0, s1 = 0;
+  if (lane < 13) {
+    // neighbour at (cx + ox_, cy + oy_), region row ry; lanes 0-2 below, 3-5
+    // above, 6-8 the three rows to the left, 9-11 to the right
+    const int k3 = lane % 3;
+    const int ox_ = lane < 6 ? k3 - 1 : (lane < 9 ? -1 : 1), oy_ = lane < 3 ? -1 : (lane < 6 ? 1 : 0);
+    const int ry = lane < 3 ? 2 : (lane < 6 ? 0 : k3);
+    const int rx0 = ox_ < 0 ? 2 : 0, rx1 = ox_ > 0 ? 0 : 2;
+    const int nc = ((cy + oy_ + d.C) % d.C) * d.C + (cx + ox_ + d.C) % d.C;
+    const int k0 = kRegions * nc + 3 * ry;
+    s0 = gload(lane == 12 ? d.cell_start + cell : d.reg_start + k0 + rx0);
+    s1 = gload(lane == 12 ? d.cell_start + cell + 1 : d.reg_start + k0 + rx1 + 1);
+  }
+  if (__builtin_amdgcn_ballot_w64(s0 < 0 || s1 < s0 || s1 - s0 > d.cap_own || (int64_t)s1 > d.n) != 0) {
     if (lane == 0) atomicOr(d.err, ERR_OWN_CAP);
     return;
   }
-  for (int i = lane; i < n_own; i += 64) tmp[i] = d.cell_ids[start + i];
+  const int start = readlane_i32(s0, 12), n_own = readlane_i32(s1, 12) - start;
+  // own disks, sorted by id: each lane counts the smaller ids of its own
+  for (int i = lane; i < ((n_own + 3) & ~3); i += 64)
+    tmp[i] = i < n_own ? gload(d.cell_ids + start + i) : 0x7FFFFFFF;
   wave_sync();
   for (int i = lane; i < n_own; i += 64) {
     int v = tmp[i];
     int r = 0;
-    for (int j = 0; j < n_own; ++j) r += (tmp[j] < v) ? 1 : 0;
+    for (int j = 0; j < n_own; j += 4) {
+      const int4 t4 = *(const int4*)(tmp + j);
+      r += (t4.x < v ? 1 : 0) + (t4.y < v ? 1 : 0) + (t4.z < v ? 1 : 0) + (t4.w < v ? 1 : 0);
+    }
     own_gid[r] = v;
   }
   wave_sync();
@@ -1200,8 +1243,8 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // reported as a capacity error)
   for (int k = lane; k < n_own; k += 64) {
     int g = own_gid[k];
-    double vx = local_coord(d.x[g], dr.sx, ox, L, half_L);
-    double vy = local_coord(d.y[g], dr.sy, oy, L, half_L);
+    double vx = local_coord(gload(d.x + g), dr.sx, ox, L, half_L);
+    double vy = local_coord(gload(d.y + g), dr.sy, oy, L, half_L);
     int bx = (int)floor(vx * d.inv_b), by = (int)floor(vy * d.inv_b);
     bx = bx < 0 ? 0 : (bx > nb - 1 ? nb - 1 : bx);
     by = by < 0 ? 0 : (by > nb - 1 ? nb - 1 : by);
@@ -1213,34 +1256,25 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
     pos[s] = make_double2(vx, vy);
     own_loc[k] = (uint16_t)s;
   }
-  // frozen disks: centres of the 8 neighbouring cells within sigma of this
-  // cell, in the two outer rings of bins.  Only a neighbour's regions that
-  // face this cell are read (its wall strips are wider than sigma, so they
-  // hold every such centre): the strip along the shared wall of an edge
-  // neighbour, the corner region of a diagonal one.  A region row is one
-  // range of the list, a region column three.
-  for (int nbh = 0; nbh < 9; ++nbh) {
-    if (nbh == 4) continue;
-    const int ox_ = nbh % 3 - 1, oy_ = nbh / 3 - 1;  // neighbour at (cx + ox_, cy + oy_)
-    int ncx = (cx + ox_ + d.C) % d.C;
-    int ncy = (cy + oy_ + d.C) % d.C;
-    int nc = ncy * d.C + ncx;
-    // its strips facing this cell: the low strip of a neighbour above or to
-    // the right, the high strip of one below or to the left, all three
-    // across an edge it shares
-    const int rx0 = ox_ > 0 ? 0 : (ox_ < 0 ? 2 : 0), rx1 = ox_ > 0 ? 0 : 2;
-    const int ry0 = oy_ > 0 ? 0 : (oy_ < 0 ? 2 : 0), ry1 = oy_ > 0 ? 0 : 2;
-    for (int ry = ry0; ry <= ry1; ++ry) {
-    const int k0 = kRegions * nc + 3 * ry;
-    int s0 = d.reg_start[k0 + rx0], s1 = d.reg_start[k0 + rx1 + 1];
-    if (s0 < 0 || s1 < s0 || s1 - s0 > d.cap_own || (int64_t)s1 > d.n) {
-      if (lane == 0) atomicOr(d.err, ERR_OWN_CAP);
-      return;
+  // frozen disks, in the two outer rings of bins: the twelve lists read as one
+  {
+    int upto = lane < 12 ? s1 - s0 : 0;  // disks of this lane's list and those before
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+      const int before = __shfl_up(upto, off, 16);
+      if ((lane & 15) >= off) upto += before;
     }
-    for (int i = s0 + lane; i < s1; i += 64) {
-      int g = d.cell_ids[i];
-      double vx = local_coord(d.x[g], dr.sx, ox, L, half_L);
-      double vy = local_coord(d.y[g], dr.sy, oy, L, half_L);
+    const int n_band = readlane_i32(upto, 11);
+    for (int i = lane; i < n_band; i += 64) {
+      int at = readlane_i32(s0, 0) + i;
+#pragma unroll
+      for (int r = 1; r < 12; ++r) {
+        const int first = readlane_i32(upto, r - 1);
+        at = i >= first ? readlane_i32(s0, r) + (i - first) : at;
+      }
+      int g = gload(d.cell_ids + at);
+      double vx = local_coord(gload(d.x + g), dr.sx, ox, L, half_L);
+      double vy = local_coord(gload(d.y + g), dr.sy, oy, L, half_L);
       if (vx >= -sigma && vx <= w + sigma && vy >= -sigma && vy <= w + sigma) {
         int bx = (int)floor(vx * d.inv_b), by = (int)floor(vy * d.inv_b);
         bx = bx < -2 ? -2 : (bx > nb + 1 ? nb + 1 : bx);
@@ -1253,7 +1287,6 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
         pos[s] = make_double2(vx, vy);
       }
     }
-    }  // region rows
   }
   wave_sync();
   if (load_err(d) != 0) return;  // a capacity check failed somewhere: do not run chains
@@ -1261,7 +1294,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   // ---- chains --------------------------------------------------------------
   const int64_t n_m = chains_of(d, n_own);
   const int64_t cbase = chain_base(d, cell);
-  double acc = d.acc_delta[cell];
+  double acc = gload(d.acc_delta + cell);
   uint32_t n_lift = 0, n_frozen = 0, n_wall = 0;
   uint64_t h = 0;
   int n_ring = 0;            // event records held in the lanes (lane k: record k)
@@ -1299,8 +1332,8 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 
   // draws of chain 0; later, those of chain k + 1 and the device error word
   // are loaded while chain k runs (their latency is then hidden)
-  int32_t nxt_start = n_m > 0 ? d.chain_start[cbase] : 0;
-  double2 nxt_dir = n_m > 0 ? d.chain_dir[cbase] : make_double2(1.0, 0.0);
+  int32_t nxt_start = n_m > 0 ? gload(d.chain_start + cbase) : 0;
+  double2 nxt_dir = n_m > 0 ? gload(d.chain_dir + cbase) : make_double2(1.0, 0.0);
   int32_t nxt_err = load_err(d);
   for (int64_t k = 0; k < n_m && aborted == 0; ++k) {
     int j = uniform_i32(nxt_start);
@@ -1308,8 +1341,8 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
     double dx = nxt_dir.x, dy = nxt_dir.y;
     stop = uniform_i32(nxt_err);
     if (k + 1 < n_m) {
-      nxt_start = d.chain_start[cbase + k + 1];
-      nxt_dir = d.chain_dir[cbase + k + 1];
+      nxt_start = gload(d.chain_start + cbase + k + 1);
+      nxt_dir = gload(d.chain_dir + cbase + k + 1);
     }
     nxt_err = load_err(d);
     // per direction: the window's origin relative to the mover's bin, and the
@@ -1337,8 +1370,9 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       ax = ap_.x;                                                                   \
       ay = ap_.y;                                                                   \
     } while (0)
+    const int slot_j = (int)own_loc[j];  // read while the direction is set
     EC_SET_DIRECTION();
-    int a_slot = uniform_i32((int)own_loc[j]);
+    int a_slot = uniform_i32(slot_j);
     int a_lidx = j;
     double ax, ay;
     double nrem = -d.ell;  // minus the chain length left
@@ -1416,6 +1450,36 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       }
       if (stop != 0 || capped != 0) continue;  // leaves the event loop
 
+      // ---- the chain end: every disk of the window is farther than the length
+      // left (by the high word of its distance), and the move by that length is
+      // one the window vouches for and ends eps inside the cell (as for plain
+      // lifts)
+      const double rem = -nrem;
+      {
+        const double ex = fma(rem, dx, ax), ey = fma(rem, dy, ay);
+        const double wall = fmax(fabs(ex - mid), fabs(ey - mid)) - inner;
+        const int calm = hi_word(rem - dsafe) & hi_word(wall) & (int)(key_min > (uint32_t)hi_word(rem) ? 0x80000000 : 0);
+        if (uniform_i32(calm) < 0) {
+          const int es = uniform_i32((int)(ey * inv_b) * gridb + (int)(ex * inv_b));
+          const uint64_t sb = (uint64_t)__double_as_longlong(rem);
+          writelane3(rec_lo, rec_hi, rec_tag, (uint32_t)sb, (uint32_t)(sb >> 32),
+                     ((uint32_t)(EV_END ^ 1) << 29) | (uint32_t)end_id, n_ring);
+          if (es != a_slot) {  // to a bin that is empty
+            pos[a_slot] = nan2;
+            meta[es] = (uint32_t)a_lidx;
+            own_loc[a_lidx] = (uint16_t)es;
+          }
+          pos[es] = make_double2(ex, ey);
+          if (REJ == 1) {  // accepted: its contact sum and lifts count
+            acc = acc + chain_acc;
+            n_lift += chain_lifts;
+          }
+          ended = 1;
+          __builtin_amdgcn_wave_barrier();
+          if (__builtin_expect(++n_ring == kDigestBatch, 0)) EC_FLUSH();
+          continue;
+        }
+      }
       // ---- any other event.  The nearest disk of the window:
       double best_s = INFINITY, wpx = 0.0, wpy = 0.0;  // (a disk can be hit exactly when best_s is finite)
       uint32_t wm = kFrozenBit;
@@ -1428,7 +1492,6 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
         wpy = readlane_f64(p.y, win);
         w_slot = readlane_i32(widx, win);
       }
-      const double rem = -nrem;
       // Where the move to the nearest disk, or by the length left if that is
       // shorter, is one the window vouches for and ends eps inside the cell, it
       // is the event (as for plain lifts): a contact or the chain end.
@@ -1649,15 +1712,15 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   for (int k = lane; k < n_own; k += 64) {
     int g = own_gid[k];
     double2 v = pos[(int)own_loc[k]];
-    double px = d.x[g], py = d.y[g];
+    double px = gload(d.x + g), py = gload(d.y + g);
     double v0x = local_coord(px, dr.sx, ox, L, half_L);
     double v0y = local_coord(py, dr.sy, oy, L, half_L);
     double nx = px + (v.x - v0x);
     double ny = py + (v.y - v0y);
     if (nx < 0.0) nx += L; else if (nx >= L) nx -= L;
     if (ny < 0.0) ny += L; else if (ny >= L) ny -= L;
-    d.x[g] = nx;
-    d.y[g] = ny;
+    gstore(d.x + g, nx);
+    gstore(d.y + g, ny);
     // (from the cell-local position, which differs from the one a neighbour
     // computes from (nx, ny) by a few ulps of L, far inside the strip margin)
     const int r = 3 * strip_of(v.y, w, d.strip) + strip_of(v.x, w, d.strip);
@@ -1668,7 +1731,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   if (lane == 0) {
     uint32_t run = (uint32_t)start;
     for (int r = 0; r < kRegions; ++r) {
-      d.reg_start[kRegions * cell + r] = (int32_t)run;
+      gstore(d.reg_start + kRegions * cell + r, (int32_t)run);
       rcnt[kRegions + r] = run;
       run += rcnt[r];
     }
@@ -1676,16 +1739,16 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   wave_sync();
   for (int k = lane; k < n_own; k += 64) {
     const uint32_t at = atomicAdd(&rcnt[kRegions + (int)own_loc[k]], 1u);
-    d.cell_ids[at] = own_gid[k];
+    gstore(d.cell_ids + at, own_gid[k]);
   }
   if (lane == 0) {
-    d.acc_delta[cell] = acc;
-    unsigned long long* c = d.acc_cnt + (size_t)cell * CNT_NCOL;
+    gstore(d.acc_delta + cell, acc);
+    EC_GLOBAL(unsigned long long)* c = (EC_GLOBAL(unsigned long long)*)(d.acc_cnt + (size_t)cell * CNT_NCOL);
     c[CNT_LIFTS] += n_lift;
     c[CNT_FROZEN] += n_frozen;
     c[CNT_WALLS] += n_wall;
     c[CNT_CHAINS] += (uint64_t)n_m;
-    d.cell_digest[cell] = h;
+    gstore(d.cell_digest + cell, (unsigned long long)h);
     atomicAdd(&d.digest_ring[sweep % kDigestRing], h * (2ull * (uint64_t)cell + 1ull));
   }
 }
@@ -1900,7 +1963,8 @@ __global__ void __launch_bounds__(256) k_queue_cells(const Dev* __restrict__ ds,
     // are visible to the loads below
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const int64_t task = rq.tasks[t];
-    const int sys = (int)(task >> 32), cell = (int)(uint32_t)task;
+    // (read as scalars, so that the record is read by scalar loads)
+    const int sys = uniform_i32((int)(task >> 32)), cell = uniform_i32((int)(uint32_t)task);
     const Dev& d = ds[sys];
     const int64_t sweep = *d.sweep_ctr;
     const SweepDraws dr = *d.draws;
