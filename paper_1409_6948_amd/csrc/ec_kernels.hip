@@ -763,11 +763,16 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // a vector use; 1 to a lane read, or from a root or reciprocal estimate to its
 // use.  Everything read from LDS has arrived where the code is left.
 //
-// Costs found by doubling single instructions (a wavefront alone on its SIMD):
-// vector and scalar instructions 4 cycles, an LDS store 22 to 34 (by its
-// width, whatever the lanes), an LDS read 8 to 15.  So words go to the other
-// lanes by lane reads and records by lane writes, not through LDS.
-// Measured, ms a sweep: 1M disks 72.8 and 65k disks 64.6, against 84.7 and 72.8
+// Costs found by doubling single instructions and by adding idle ones (a
+// wavefront alone on its SIMD): vector and scalar instructions 4 cycles, an LDS
+// store 22 to 34 (by its width, whatever the lanes), an LDS read 8 to 15, and a
+// scalar instruction waits about 16 cycles for any vector instruction that wrote
+// a scalar register just before, its own operand or not.  So words go to the
+// other lanes by lane reads and records by lane writes, not through LDS; and the
+// lane reads stand together, with vector work or the LDS store between them and
+// the next scalar instruction (the contact sum and term stand where they do for
+// that alone: 1M disks 72.4 -> 67.1 ms a sweep).
+// Measured, ms a sweep: 1M disks 67.1 and 65k disks 60.0, against 84.7 and 72.8
 // with what the winner has to tell sent through LDS and reflections left to the
 // general path, and about 97 and 84 with the loop compiled from C++.
 #define EC_W(x) x "\n\t"
@@ -799,14 +804,14 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // walled cells: rows clamped to the grid
 #define EC_READ_WINDOW                                                                         \
   EC_W("s_mul_hi_u32 %[t], %[a_slot], %[inv_g32]")                                             \
-  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
   EC_W("s_add_i32 %[u], %[t], %[offy]")                                                        \
+  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
   EC_W("s_min_i32 %[u], %[u], %[top]")                                                         \
   EC_W("s_max_i32 %[u], %[u], -2")                                                             \
   EC_W("s_sub_i32 %[u], %[u], %[t]")                                                           \
   EC_W("s_mul_i32 %[u], %[u], %[gridb]")                                                       \
   EC_W("s_add_i32 %[u], %[u], %[a_slot]")                                                      \
-  EC_W("v_add_u32_e64 v69, %[u], %[woff]")                                                     \
+  EC_W("v_add_u32_e32 v69, %[u], %[woff]")                                                     \
   EC_READ_SLOTS
 // the moved centre changes bin, to one that is empty (a bin holds one centre):
 // the old slot is emptied, and the disk's meta word and slot index move
@@ -822,7 +827,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("ds_write_b32 v125, v126")                                                              \
   EC_W("v_lshl_add_u32 v125, %[a_lidx], 1, %[own_loc]")                                        \
   EC_W("ds_write_b16 v125, v123")
-// one event; K numbers its labels, BACK goes on to the next event
+// one event; K numbers its labels, BACK is what stands at its end
 #define EC_EVENT(K, IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, BACK)                                                   \
   EC_W("s_waitcnt lgkmcnt(0)")                                                                 \
   /* contact distance */                                                                       \
@@ -835,7 +840,6 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_fmac_f64_e32 v[114:115], v[110:111], v[80:81]")                                      \
   EC_W("v_fma_f64 v[116:117], -v[112:113], v[112:113], %[sig2]")                               \
   EC_W("v_rsq_f64_e64 v[118:119], v[116:117]")                                                 \
-  EC_W("v_add_f64 v[78:79], v[78:79], s[92:93]")                                               \
   EC_W("v_min_f64 v[112:113], v[114:115], v[116:117]")                                         \
   EC_W("v_mul_f64 v[108:109], v[116:117], v[118:119]")                                         \
   EC_W("v_mul_f64 v[118:119], v[118:119], 0.5")                                                \
@@ -870,38 +874,37 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_add_f64 v[100:101], v[96:97], s[90:91]")                                             \
   EC_W("v_min_u32_dpp v121, v121, v121 row_bcast:31 row_mask:0xc bank_mask:0xf")               \
   EC_W("v_add_f64 v[110:111], v[96:97], -v[84:85]")                                            \
-  EC_W("v_and_b32_e64 v122, v101, v109")                                                       \
   EC_W("v_readlane_b32 %[kmin], v121, 63")                                                     \
+  EC_W("v_and_b32_e64 v122, v101, v109")                                                       \
   EC_W("v_bitop3_b32 v122, v122, v111, v98 bitop3:0x40") /* a & b & ~c */                      \
-  EC_W("v_bfi_b32 v122, %[low31], v123, v122")                                                 \
   EC_W("v_cmp_eq_u32_e64 %[mask], %[kmin], v120")                                              \
+  EC_W("v_bfi_b32 v122, %[low31], v123, v122")                                                 \
   /* the contact term */                                                                       \
+  EC_W("v_add_f64 v[78:79], v[78:79], s[92:93]")                                               \
   EC_W("v_add_f64 v[112:113], v[64:65], -v[104:105]")                                          \
   EC_W("v_add_f64 v[114:115], v[66:67], -v[106:107]")                                          \
+  EC_W("s_mov_b64 exec, %[mask]")                                                              \
+  EC_W("v_readfirstlane_b32 %[t], v122")                                                       \
+  EC_W("v_lshl_add_u32 v124, v123, 4, %[pos]")                                                 \
   TERM_IMAGE                                                                                   \
   EC_W("v_mul_f64 v[102:103], v[82:83], v[114:115]")                                           \
   EC_W("v_fmac_f64_e64 v[102:103], v[112:113], v[80:81]")                                      \
-  EC_W("v_lshl_add_u32 v124, v123, 4, %[pos]")                                                 \
-  /* from here the winner alone: one lane, and its code is "plain, same slot" */               \
-  EC_W("s_mov_b64 exec, %[mask]")                                                              \
-  EC_W("v_readfirstlane_b32 %[t], v122")                                                       \
   EC_W("s_bcnt1_i32_b64 %[u], %[mask]")                                                        \
-  EC_W("v_readfirstlane_b32 %[slo], v96")                                                      \
-  EC_W("v_readfirstlane_b32 %[shi], v97")                                                      \
-  EC_W("v_readfirstlane_b32 s92, v102")                                                        \
-  EC_W("v_readfirstlane_b32 s93, v103")                                                        \
   EC_W("s_add_i32 %[u], %[u], -1")                                                             \
   EC_W("s_xor_b32 %[t], %[t], %[expect]")                                                      \
   EC_W("s_or_b32 %[u], %[u], %[t]")                                                            \
   EC_W("s_cbranch_scc1 3" K "f")                                                               \
   EC_W("4" K ":")                                                                              \
-  EC_W("v_readfirstlane_b32 %[next], v69")                                                     \
-  EC_W("ds_write_b128 v124, v[104:107]")                                                       \
-  EC_W("v_readfirstlane_b32 s90, v100")                                                        \
-  EC_W("v_readfirstlane_b32 s91, v101")                                                        \
   EC_W("v_readfirstlane_b32 %[a_lidx], v98")                                                   \
   LOG                                                                                          \
-  EC_W("s_mov_b32 %[a_slot], %[next]")                                                         \
+  EC_W("v_readfirstlane_b32 %[a_slot], v69")                                                   \
+  EC_W("v_readfirstlane_b32 %[slo], v96")                                                      \
+  EC_W("v_readfirstlane_b32 %[shi], v97")                                                      \
+  EC_W("v_readfirstlane_b32 s92, v102")                                                        \
+  EC_W("v_readfirstlane_b32 s93, v103")                                                        \
+  EC_W("v_readfirstlane_b32 s90, v100")                                                        \
+  EC_W("v_readfirstlane_b32 s91, v101")                                                        \
+  EC_W("ds_write_b128 v124, v[104:107]")                                                       \
   EC_W("s_mov_b64 exec, -1")                                                                   \
   STEP                                                                                         \
   WINDOW                                                                                       \
@@ -910,7 +913,6 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_writelane_b32 v95, %[shi], m0")                                                      \
   EC_W("v_writelane_b32 v99, %[a_lidx], m0")                                                   \
   EC_W("s_add_i32 m0, m0, 1")                                                                  \
-  EC_W("s_cmp_eq_u32 m0, %[limit]")                                                            \
   BACK
 // beside the loop: ties, bin changes, reflections
 #define EC_ASIDE(K, FROZEN)                                                                    \
@@ -935,6 +937,10 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("s_cbranch_scc1 2f")                                                                    \
   EC_W("v_readfirstlane_b32 s90, v100")                                                        \
   EC_W("v_readfirstlane_b32 s91, v101")                                                        \
+  EC_W("v_readfirstlane_b32 %[slo], v96")                                                      \
+  EC_W("v_readfirstlane_b32 %[shi], v97")                                                      \
+  EC_W("v_readfirstlane_b32 s92, v102")                                                        \
+  EC_W("v_readfirstlane_b32 s93, v103")                                                        \
   /* the normal n = r / |r| of r (v112, v114) */                                               \
   EC_W("v_mul_f64 v[108:109], v[114:115], v[114:115]")                                         \
   EC_W("v_fmac_f64_e32 v[108:109], v[112:113], v[112:113]")                                    \
@@ -990,9 +996,17 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("s_mov_b32 %[a_slot], %[next]")                                                         \
   EC_READ_WINDOW                                                                               \
   EC_W("s_add_i32 m0, m0, 1")                                                                  \
-  EC_W("s_cmp_lg_u32 m0, %[limit]")                                                            \
+  EC_W("s_sub_i32 %[t], m0, %[limit]")                                                         \
+  EC_W("s_cmp_eq_u32 %[t], 0")                                                                 \
+  EC_W("s_cbranch_scc1 5f")                                                                    \
+  EC_W("s_and_b32 %[t], %[t], 3")                                                              \
+  EC_W("s_cmp_eq_u32 %[t], 0")                                                                 \
   EC_W("s_cbranch_scc1 1b")                                                                    \
-  EC_W("s_branch 5f")
+  EC_W("s_cmp_eq_u32 %[t], 1")                                                                 \
+  EC_W("s_cbranch_scc1 12b")                                                                   \
+  EC_W("s_cmp_eq_u32 %[t], 2")                                                                 \
+  EC_W("s_cbranch_scc1 13b")                                                                   \
+  EC_W("s_branch 14b")
 // the way out: at the limit (5), or with an event that is another one (2)
 #define EC_LEAVE                                                                               \
   EC_W("5:")                                                                                   \
@@ -1006,23 +1020,43 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("s_waitcnt lgkmcnt(0)")                                                                 \
   EC_W("9:")                                                                                   \
   "s_nop 4"
-// A second copy of the event saves every other taken branch (four are no faster).
+// Four copies of the event, of which only the last looks at the limit and takes
+// a branch (14 cycles each time): the loop is entered at the copy from which the
+// limit is reached at the end of the last.
 // The code is laid out so that no 8-byte instruction crosses an 8-byte boundary:
 // in a run of such instructions each costs a cycle more where they do.  So 4-byte
 // instructions come in pairs, single ones in their 8-byte encoding (_e64), and
 // the loop starts 4 bytes past a 32-byte boundary.
+#define EC_ENTER                                                                               \
+  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
+  EC_W("s_sub_i32 %[t], m0, %[limit]")                                                         \
+  EC_W("s_and_b32 %[t], %[t], 3")                                                              \
+  EC_W("s_cmp_eq_u32 %[t], 1")                                                                 \
+  EC_W("s_cbranch_scc1 12f")                                                                   \
+  EC_W("s_cmp_eq_u32 %[t], 2")                                                                 \
+  EC_W("s_cbranch_scc1 13f")                                                                   \
+  EC_W("s_cmp_eq_u32 %[t], 3")                                                                 \
+  EC_W("s_cbranch_scc1 14f")                                                                   \
+  EC_W(".p2align 5")                                                                           \
+  EC_W("s_nop 0")                                                                              \
+  EC_W("1:")
+#define EC_BACK                                                                                \
+  EC_W("s_cmp_lg_u32 m0, %[limit]")                                                            \
+  EC_W("s_cbranch_scc1 1b")                                                                    \
+  EC_W("s_branch 5f")
+#define EC_FOUR(IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, FROZEN)                                  \
+  EC_ENTER                                                                                     \
+  EC_EVENT("1", IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, EC_W("12:"))                             \
+  EC_EVENT("2", IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, EC_W("13:"))                             \
+  EC_EVENT("3", IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, EC_W("14:"))                             \
+  EC_EVENT("4", IMAGE, TERM_IMAGE, WINDOW, LOG, STEP, EC_BACK)                                 \
+  EC_ASIDE("1", FROZEN)                                                                        \
+  EC_ASIDE("2", FROZEN)                                                                        \
+  EC_ASIDE("3", FROZEN)                                                                        \
+  EC_ASIDE("4", FROZEN)
 #define EC_LOOP(LOG, STEP, FROZEN, REFLECTION, UNDO)                                           \
   asm volatile(                                                                                \
-      EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                        \
-      EC_W("s_nop 3")                                                                          \
-      EC_W(".p2align 5")                                                                       \
-      EC_W("s_nop 0")                                                                          \
-      EC_W("1:")                                                                               \
-      EC_EVENT("1", , , EC_READ_WINDOW, LOG, STEP, EC_W("s_cbranch_scc1 5f"))                  \
-      EC_EVENT("2", , , EC_READ_WINDOW, LOG, STEP, EC_W("s_cbranch_scc0 1b"))                  \
-      EC_W("s_branch 5f")                                                                      \
-      EC_ASIDE("1", FROZEN)                                                                    \
-      EC_ASIDE("2", FROZEN)                                                                    \
+      EC_FOUR(, , EC_READ_WINDOW, LOG, STEP, FROZEN)                                           \
       REFLECTION                                                                               \
       EC_LEAVE                                                                                 \
       : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(widx), "+{v[70:71]}"(ax),             \
@@ -1063,11 +1097,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // the free-flight cap L / 2 - sigma).  v - n L is then one rounding of v - L,
 // v or v + L, as there.  A lift across the box edge is not plain (the moved
 // centre's test against the walls of a cell is one against the box here).
-// 256 disks: 28.8 -> 15.5 ms a sweep against the loop compiled from C++.
+// 256 disks: 28.8 -> 13.9 ms a sweep against the loop compiled from C++.
 #define EC_READ_PERIODIC                                                                       \
   EC_W("s_mul_hi_u32 %[t], %[a_slot], %[inv_g32]")                                             \
-  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
   EC_W("s_mul_i32 %[u], %[t], %[gridb]")                                                       \
+  EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                            \
   EC_W("s_sub_i32 %[u], %[a_slot], %[u]")                                                      \
   EC_W("s_add_i32 %[u], %[u], %[offx]")                                                        \
   EC_W("s_add_i32 %[t], %[t], %[offy]")                                                        \
@@ -1095,16 +1129,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("v_fma_f64 v[114:115], -v[86:87], %[L], v[114:115]")
 #define EC_LOOP_PERIODIC                                                                       \
   asm volatile(                                                                                \
-      EC_W("s_or_b32 %[expect], %[a_slot], 0x80000000")                                        \
-      EC_W("s_nop 3")                                                                          \
-      EC_W(".p2align 5")                                                                       \
-      EC_W("s_nop 0")                                                                          \
-      EC_W("1:")                                                                               \
-      EC_EVENT("1", EC_NEAREST_IMAGE, EC_TERM_IMAGE, EC_READ_PERIODIC, , , EC_W("s_cbranch_scc1 5f")) \
-      EC_EVENT("2", EC_NEAREST_IMAGE, EC_TERM_IMAGE, EC_READ_PERIODIC, , , EC_W("s_cbranch_scc0 1b")) \
-      EC_W("s_branch 5f")                                                                      \
-      EC_ASIDE("1", "2f")                                                                      \
-      EC_ASIDE("2", "2f")                                                                      \
+      EC_FOUR(EC_NEAREST_IMAGE, EC_TERM_IMAGE, EC_READ_PERIODIC, , , "2f")                     \
       EC_LEAVE                                                                                 \
       : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(wsl), "+{v[70:71]}"(ax),              \
         "+{v[72:73]}"(ay), "+{s[90:91]}"(nrem), "+{s[92:93]}"(dacc), "+{v[78:79]}"(acc),       \
