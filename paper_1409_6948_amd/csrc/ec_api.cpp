@@ -19,7 +19,7 @@ namespace {
 constexpr double kPi = 3.14159265358979323846;
 
 struct Layout {
-  size_t dev, sweep_ctr, x, y, cell_of, reg_of, cell_ids, reg_count, reg_fill, cell_start, reg_start,
+  size_t dev, sweep_ctr, x, y, cell_of, reg_of, cell_ids, reg_count, cell_start, reg_start,
       acc_delta, acc_cnt,
       ring, cell_digest, draws, err, red, chain_start, chain_dir, shuffle, dbg, psi, psi_part, psi_red,
       gr, queue, cell_done, psi_nb, psi_err, obs_pos, obs_id, obs_list, obs_count, obs_range, obs_ctr, ovl, total;
@@ -49,7 +49,6 @@ Layout make_layout(int64_t n, int32_t C, int32_t chains_per_cell, bool sweep_onl
   l.reg_of = o;     o = align256(o + (size_t)n);
   l.cell_ids = o;   o = align256(o + 4 * (size_t)n);
   l.reg_count = o;  o = align256(o + 4 * nr);
-  l.reg_fill = o;   o = align256(o + 4 * nr);
   l.cell_start = o; o = align256(o + 4 * (nc + 1));
   l.reg_start = o;  o = align256(o + 4 * (nr + 1));
   l.acc_delta = o;  o = align256(o + 8 * nc);
@@ -357,7 +356,6 @@ void fill_record(ec::Dev* out, const ec_params* p, const Derived& dv, unsigned c
   d.cell_of = (int32_t*)(b + lay.cell_of);
   d.cell_ids = (int32_t*)(b + lay.cell_ids);
   d.reg_count = (int32_t*)(b + lay.reg_count);
-  d.reg_fill = (int32_t*)(b + lay.reg_fill);
   d.reg_start = (int32_t*)(b + lay.reg_start);
   d.reg_of = (uint8_t*)(b + lay.reg_of);
   d.cell_start = (int32_t*)(b + lay.cell_start);
@@ -470,7 +468,7 @@ ec_status init_system_at(const ec_params* p, const Derived& dv, unsigned char* b
   double a = dv.L / (double)k;
   hipError_t e = prepare_kernels();
   if (e == hipSuccess) e = hipMemcpyAsync(s->dev_d, &s->dev, sizeof(ec::Dev), hipMemcpyHostToDevice, stream);
-  if (e == hipSuccess) e = hipMemsetAsync(d.sweep_ctr, 0, 8, stream);
+  if (e == hipSuccess) e = hipMemsetAsync(d.sweep_ctr, 0xFF, 8, stream);
   if (e == hipSuccess) e = ec::launch_lattice(s->dev_d, d.n, k, a, stream);
   if (e == hipSuccess) e = ec::launch_zero_tallies(s->dev_d, d.C * d.C, stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.err, 0, 8, stream);

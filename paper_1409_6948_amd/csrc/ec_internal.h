@@ -79,7 +79,6 @@ struct Dev {
   double* x;                        // [N] positions, disk-id order
   double* y;
   int32_t* reg_count;               // [9*C*C] disks per (cell, region)
-  int32_t* reg_fill;                // [9*C*C]
   int32_t* cell_start;              // [C*C+1] exclusive prefix sum over cells
   int32_t* reg_start;               // [9*C*C+1] exclusive prefix sum over (cell, region)
   int32_t* cell_of;                 // [N]
@@ -94,9 +93,10 @@ struct Dev {
   double* red;                      // [8]: reduced tallies (double sum + counters as bits)
   int32_t* chain_start;             // [max chains per sweep] start index within its cell
   double2* chain_dir;               // [max chains per sweep] direction of each chain
-  int32_t* shuffle;                 // [N] per-cell shuffled lists (distinct-start mode)
+  int32_t* shuffle;                 // [N] rebin: places in the (cell, region) lists; then per-cell
+                                    // shuffled lists (distinct-start mode)
   double* dbg;                      // [kDebugWords] state of the first wave that tripped a cap
-  int64_t* sweep_ctr;               // [1] sweeps done; read by every kernel of a sweep
+  int64_t* sweep_ctr;               // [1] number of the current or last sweep, -1 before the first
   double2* psi;                     // [N] per-disk hexatic order Psi_k (re, im)
   double* psi_part;                 // [3 * ceil(N/256)] per-block sums (re, im, neighbours)
   double* psi_red;                  // [3] Psi (re, im) and the mean neighbour count
@@ -222,9 +222,9 @@ struct PhaseEvents {
 };
 
 hipError_t launch_lattice(const Dev* ds, int64_t n, int64_t k, double a, hipStream_t st);
-// One sweep of every system in ds: rebin, draws, four colour phases (or the
-// periodic kernel), then the sweep counters advance.  Kernels only (no memset
-// or copy), so the sequence can be captured in a HIP graph and replayed.
+// One sweep of every system in ds: the sweep counters advance, rebin, draws,
+// four colour phases (or the periodic kernel).  Kernels only (no memset or
+// copy), so the sequence can be captured in a HIP graph and replayed.
 hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
                         const PhaseEvents* ev = nullptr);
 hipError_t launch_reduce(const Dev* ds, hipStream_t st);
@@ -253,7 +253,7 @@ constexpr int64_t kStaticMaxDisks = int64_t(1) << 18;
 // Address of this GPU's static buffer (looked up once per device).
 hipError_t static_scratch(void** ptr);
 // Clear [base, base + bytes) with a kernel, then store rec at dst and the
-// number of the first sweep in rec.sweep_ctr.
+// sweep counter before the first sweep in rec.sweep_ctr.
 hipError_t launch_static_setup(const Dev& rec, Dev* dst, unsigned char* base, size_t bytes,
                                int64_t first_sweep, hipStream_t st);
 // Digests of sweeps first .. first + n - 1 and the device error word into

@@ -392,20 +392,20 @@ __device__ int32_t decode_perm(uint64_t idx) {
   return out;
 }
 
-// squares = 0: the sweep's own decomposition (stripes for a striped system);
-// 1: the square cells that the observables' rebin always uses.
-__global__ void k_prep(const Dev* __restrict__ ds, int squares) {
+// The first kernel of a sweep: its number (the counter holds that of the last
+// sweep, -1 before the first), its draws, cleared counts.
+__global__ void k_prep(const Dev* __restrict__ ds) {
   const Dev& d = ds[blockIdx.y];
-  const int64_t sweep = *d.sweep_ctr;
   const int nreg = kRegions * d.C * d.C;
   for (int c = threadIdx.x; c < nreg; c += blockDim.x) {
     d.reg_count[c] = 0;
-    d.reg_fill[c] = 0;
   }
   if (threadIdx.x == 0) {
+    const int64_t sweep = *d.sweep_ctr + 1;
+    *d.sweep_ctr = sweep;
     Stream st(d.seed, kKindSweep, (uint64_t)sweep, (uint64_t)d.system, 0);
     SweepDraws dr;
-    if (d.stripes && !squares) {
+    if (d.stripes) {
       // stripes: shift across them, and which of the two colours goes first
       dr.sx = u01(st.next()) * d.w;
       dr.sy = 0.0;
@@ -437,13 +437,31 @@ __device__ __forceinline__ int strip_of(double v, double w, double strip) {
   return v < strip ? 0 : (v >= w - strip ? 2 : 1);
 }
 
-__global__ void k_count(const Dev* __restrict__ ds, int squares) {
+// Lanes of the wave whose key equals this lane's (among the lanes that run).
+__device__ __forceinline__ uint64_t lanes_of_key(int key) {
+  uint64_t todo = __builtin_amdgcn_ballot_w64(true), mine = 0;
+  while (todo) {
+    const int lk = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(todo));
+    const uint64_t same = __builtin_amdgcn_ballot_w64(key == lk);
+    if (key == lk) mine = same;
+    todo &= ~same;
+  }
+  return mine;
+}
+
+// Cell and region of every disk, the counts, and each disk's place in its
+// (cell, region): one atomic per distinct (cell, region) of the wavefront
+// (consecutive ids are mostly neighbours in space, so a wave's disks fall into a
+// few), all of them at once, so that a wave waits for one trip to memory.  The
+// place is kept for k_scatter (in the array of the shuffled lists, which are
+// made after it); the order inside a region is free: staging sorts a cell's ids.
+__global__ void k_count(const Dev* __restrict__ ds) {
   const Dev& d = ds[blockIdx.y];
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= d.n) return;
   SweepDraws dr = *d.draws;
   int c, r = 0;  // cell and region (stripes and one periodic cell: region 0)
-  if (d.stripes && !squares) {
+  if (d.stripes) {
     // stripe index from the coordinate across the stripes: horizontal stripes
     // (across = y) on even sweeps, vertical ones (across = x) on odd sweeps
     const double across = (*d.sweep_ctr & 1) ? d.x[i] : d.y[i];
@@ -462,17 +480,13 @@ __global__ void k_count(const Dev* __restrict__ ds, int squares) {
   }
   d.cell_of[i] = c;
   d.reg_of[i] = (uint8_t)r;
-  // one atomic per distinct (cell, region) of the wavefront: consecutive ids
-  // are mostly neighbours in space, so a wave's disks fall into a few cells
   const int key = kRegions * c + r;
-  uint64_t todo = __builtin_amdgcn_ballot_w64(true);
-  while (todo) {
-    const int leader = (int)__builtin_ctzll(todo);
-    const int lk = __builtin_amdgcn_readlane(key, leader);
-    const uint64_t same = __builtin_amdgcn_ballot_w64(key == lk) & todo;
-    if ((threadIdx.x & 63) == (unsigned)leader) atomicAdd(&d.reg_count[lk], (int)__builtin_popcountll(same));
-    todo &= ~same;
-  }
+  const uint64_t mine = lanes_of_key(key);
+  const int lane = (int)(threadIdx.x & 63), leader = (int)__builtin_ctzll(mine);
+  int base = 0;
+  if (lane == leader) base = atomicAdd(&d.reg_count[key], (int)__builtin_popcountll(mine));
+  base = __shfl(base, leader, 64);
+  d.shuffle[i] = base + (int)__builtin_popcountll(mine & ((1ull << lane) - 1));
 }
 
 // Exclusive prefix sum of the (cell, region) counts, one workgroup of 1024
@@ -556,24 +570,7 @@ __global__ void k_scatter(const Dev* __restrict__ ds) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= d.n) return;
   const int k = kRegions * d.cell_of[i] + (int)d.reg_of[i];
-  // one atomic per distinct (cell, region) of the wavefront; each lane's slot
-  // is the group's base plus its rank among the group's lanes (the order
-  // inside a region is free: staging sorts a cell's ids)
-  const int lane = (int)(threadIdx.x & 63);
-  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint64_t todo = __builtin_amdgcn_ballot_w64(true);
-  int slot = 0;
-  while (todo) {
-    const int leader = (int)__builtin_ctzll(todo);
-    const int lk = __builtin_amdgcn_readlane(k, leader);
-    const uint64_t same = __builtin_amdgcn_ballot_w64(k == lk) & todo;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&d.reg_fill[lk], (int)__builtin_popcountll(same));
-    base = __builtin_amdgcn_readlane(base, leader);
-    if (k == lk) slot = base + (int)__builtin_popcountll(same & below);
-    todo &= ~same;
-  }
-  d.cell_ids[d.reg_start[k] + slot] = (int32_t)i;
+  d.cell_ids[d.reg_start[k] + d.shuffle[i]] = (int32_t)i;
 }
 
 // ---------------------------------------------------------------------------
@@ -2238,7 +2235,7 @@ __global__ void __launch_bounds__(64) k_stripe_phase(const Dev* __restrict__ ds,
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_periodic(const Dev* __restrict__ ds) {
   const Dev& d = ds[blockIdx.y];
-  const int64_t sweep = *d.sweep_ctr;
+  const int64_t sweep = *d.sweep_ctr + 1;  // (no k_prep before it)
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lane = threadIdx.x;
   const int n = (int)d.n;
@@ -2338,6 +2335,7 @@ __global__ void __launch_bounds__(64) k_periodic(const Dev* __restrict__ ds) {
     d.acc_cnt[CNT_PSEUDO] += n_pseudo;
     d.digest_ring[sweep % kDigestRing] = h;
     d.cell_digest[0] = h;
+    *d.sweep_ctr = sweep;
   }
 }
 
@@ -2387,7 +2385,7 @@ __global__ void k_zero_tallies(const Dev* __restrict__ ds) {
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_periodic_bins(const Dev* __restrict__ ds) {
   const Dev& d = ds[blockIdx.y];
-  const int64_t sweep = *d.sweep_ctr;
+  const int64_t sweep = *d.sweep_ctr + 1;  // (no k_prep before it)
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lane = threadIdx.x;
   const int n = (int)d.n;
@@ -2445,7 +2443,10 @@ __global__ void __launch_bounds__(64) k_periodic_bins(const Dev* __restrict__ ds
     }
   }
   wave_sync();
-  if (load_err(d) != 0) return;  // two disks in one bin: an overlap
+  if (load_err(d) != 0) {  // two disks in one bin: an overlap
+    if (lane == 0) *d.sweep_ctr = sweep;
+    return;
+  }
 
   double acc = d.acc_delta[0];
   uint64_t n_lift = 0, n_pseudo = 0, h = 0;
@@ -2661,12 +2662,8 @@ __global__ void __launch_bounds__(64) k_periodic_bins(const Dev* __restrict__ ds
     d.acc_cnt[CNT_PSEUDO] += n_pseudo;
     d.digest_ring[sweep % kDigestRing] = h;
     d.cell_digest[0] = h;
+    *d.sweep_ctr = sweep;
   }
-}
-
-// The sweep counter every kernel of the next sweep reads (one thread per system).
-__global__ void k_sweep_done(const Dev* __restrict__ ds) {
-  if (threadIdx.x == 0) *ds[blockIdx.y].sweep_ctr += 1;
 }
 
 }  // namespace
@@ -2733,13 +2730,12 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
     if (ev) (void)hipEventRecord(ev->end[0], st);
     hipError_t e = launch_check_overlap(ds, sh, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sweep_done, dim3(1, ns), dim3(64), 0, st, ds);
     return hipGetLastError();
   }
   const unsigned nblk = (unsigned)((sh.max_n + 255) / 256);
-  hipLaunchKernelGGL(k_prep, dim3(1, ns), dim3(1024), 0, st, ds, 0);
+  hipLaunchKernelGGL(k_prep, dim3(1, ns), dim3(1024), 0, st, ds);
   if (ev) (void)hipEventRecord(ev->rebin[0], st);
-  hipLaunchKernelGGL(k_count, dim3(nblk, ns), dim3(256), 0, st, ds, 0);
+  hipLaunchKernelGGL(k_count, dim3(nblk, ns), dim3(256), 0, st, ds);
   if (ev) (void)hipEventRecord(ev->rebin[1], st);
   hipLaunchKernelGGL(k_scan, dim3(1, ns), dim3(1024), 0, st, ds);
   if (ev) (void)hipEventRecord(ev->rebin[2], st);
@@ -2761,7 +2757,6 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
     }
     hipError_t e = launch_check_overlap(ds, sh, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sweep_done, dim3(1, ns), dim3(64), 0, st, ds);
     return hipGetLastError();
   }
   const int cpb = sh.cpb;
@@ -2784,7 +2779,6 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
     hipLaunchKernelGGL(k_queue_check, dim3(1, ns), dim3(64), 0, st, ds, rq);
     hipError_t e = launch_check_overlap(ds, sh, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sweep_done, dim3(1, ns), dim3(64), 0, st, ds);
     return hipGetLastError();
   }
   if (sh.one_launch) {
@@ -2797,7 +2791,6 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
     if (ev) (void)hipEventRecord(ev->end[0], st);
     hipError_t e = launch_check_overlap(ds, sh, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sweep_done, dim3(1, ns), dim3(64), 0, st, ds);
     return hipGetLastError();
   }
   for (int q = 0; q < 4; ++q) {
@@ -2810,16 +2803,6 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
   }
   hipError_t e = launch_check_overlap(ds, sh, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sweep_done, dim3(1, ns), dim3(64), 0, st, ds);
-  return hipGetLastError();
-}
-
-hipError_t launch_rebin(const Dev* ds, const LaunchShape& sh, hipStream_t st) {
-  const unsigned nblk = (unsigned)((sh.max_n + 255) / 256);
-  hipLaunchKernelGGL(k_prep, dim3(1, 1), dim3(1024), 0, st, ds, 1);
-  hipLaunchKernelGGL(k_count, dim3(nblk, 1), dim3(256), 0, st, ds, 1);
-  hipLaunchKernelGGL(k_scan, dim3(1, 1), dim3(1024), 0, st, ds);
-  hipLaunchKernelGGL(k_scatter, dim3(nblk, 1), dim3(256), 0, st, ds);
   return hipGetLastError();
 }
 

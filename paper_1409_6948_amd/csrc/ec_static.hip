@@ -32,7 +32,7 @@ __global__ void k_fill_zero(unsigned long long* p, size_t words) {
 __global__ void k_store_record(Dev rec, Dev* dst, int64_t first_sweep) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     *dst = rec;
-    *rec.sweep_ctr = first_sweep;
+    *rec.sweep_ctr = first_sweep - 1;  // advanced by the first kernel of a sweep
   }
 }
 
