@@ -21,8 +21,8 @@ constexpr double kPi = 3.14159265358979323846;
 struct Layout {
   size_t dev, sweep_ctr, x, y, cell_of, reg_of, cell_ids, reg_count, cell_start, reg_start,
       acc_delta, acc_cnt,
-      ring, cell_digest, draws, err, red, chain_start, chain_dir, shuffle, dbg, psi, psi_part, psi_red,
-      gr, queue, cell_done, psi_nb, psi_err, obs_pos, obs_id, obs_list, obs_count, obs_range, obs_ctr, ovl, total;
+      ring, cell_digest, draws, status, chain_start, chain_dir, shuffle, psi, psi_part,
+      gr, queue, cell_done, psi_nb, obs_pos, obs_id, obs_list, obs_count, obs_range, obs_ctr, total;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -56,27 +56,22 @@ Layout make_layout(int64_t n, int32_t C, int32_t chains_per_cell, bool sweep_onl
   l.ring = o;       o = align256(o + 8 * (size_t)ec::kDigestRing);
   l.cell_digest = o; o = align256(o + 8 * nc);
   l.draws = o;      o = align256(o + sizeof(ec::SweepDraws));
-  l.err = o;        o = align256(o + 8);
-  l.red = o;        o = align256(o + 64);
+  l.status = o;     o = align256(o + sizeof(ec::Status));
   l.chain_start = o; o = align256(o + 4 * max_chains);
   l.chain_dir = o;  o = align256(o + 16 * max_chains);
   l.shuffle = o;    o = align256(o + (C == 1 ? 0 : 4 * (size_t)n));
-  l.dbg = o;        o = align256(o + 8 * ec::kDebugWords);
   l.psi = o;        o = align256(o + 16 * no);
   l.psi_part = o;   o = align256(o + 24 * ((no + 255) / 256));
-  l.psi_red = o;    o = align256(o + (sweep_only ? 0 : 32));
   l.gr = o;         o = align256(o + (sweep_only ? 0 : 8 * (size_t)(ec::kMaxGrBins + 1)));
   l.queue = o;      o = align256(o + 8);
   l.cell_done = o;  o = align256(o + 8 * nc);
   l.psi_nb = o;     o = align256(o + 4 * no);
-  l.psi_err = o;    o = align256(o + (sweep_only ? 0 : 16));
   l.obs_pos = o;    o = align256(o + 16 * no);
   l.obs_id = o;     o = align256(o + 4 * no);
   l.obs_list = o;   o = align256(o + 4 * no);
   l.obs_count = o;  o = align256(o + 4 * no);
   l.obs_range = o;  o = align256(o + 8 * no);
   l.obs_ctr = o;    o = align256(o + (sweep_only ? 0 : 4 * (size_t)ec::kObsCounters));
-  l.ovl = o;        o = align256(o + 32);
   l.total = o;
   return l;
 }
@@ -364,28 +359,26 @@ void fill_record(ec::Dev* out, const ec_params* p, const Derived& dv, unsigned c
   d.digest_ring = (unsigned long long*)(b + lay.ring);
   d.cell_digest = (unsigned long long*)(b + lay.cell_digest);
   d.draws = (ec::SweepDraws*)(b + lay.draws);
-  d.err = (int32_t*)(b + lay.err);
-  d.red = (double*)(b + lay.red);
+  d.status = (ec::Status*)(b + lay.status);
+  d.err = d.status->err;
+  d.dbg = d.status->dbg;
+  d.ovl = d.status->ovl;
   d.chain_start = (int32_t*)(b + lay.chain_start);
   d.chain_dir = (double2*)(b + lay.chain_dir);
   d.shuffle = (int32_t*)(b + lay.shuffle);
-  d.dbg = (double*)(b + lay.dbg);
   d.sweep_ctr = (int64_t*)(b + lay.sweep_ctr);
   d.psi = (double2*)(b + lay.psi);
   d.psi_part = (double*)(b + lay.psi_part);
-  d.psi_red = (double*)(b + lay.psi_red);
   d.gr_counts = (unsigned long long*)(b + lay.gr);
   d.queue = (int32_t*)(b + lay.queue);
   d.cell_done = (int64_t*)(b + lay.cell_done);
   d.psi_nb = (int32_t*)(b + lay.psi_nb);
-  d.psi_err = (unsigned long long*)(b + lay.psi_err);
   d.obs_pos = (double2*)(b + lay.obs_pos);
   d.obs_id = (int32_t*)(b + lay.obs_id);
   d.obs_list = (int32_t*)(b + lay.obs_list);
   d.obs_count = (int32_t*)(b + lay.obs_count);
   d.obs_range = (int2*)(b + lay.obs_range);
   d.obs_ctr = (int32_t*)(b + lay.obs_ctr);
-  d.ovl = (unsigned long long*)(b + lay.ovl);
   d.check_overlap = (p->flags & EC_FLAG_CHECK_OVERLAP) ? 1 : 0;
   d.stripes = (p->flags & EC_FLAG_STRIPES) ? 1 : 0;
   d.stripe_cap_own = dv.stripe_cap_own;
@@ -471,13 +464,11 @@ ec_status init_system_at(const ec_params* p, const Derived& dv, unsigned char* b
   if (e == hipSuccess) e = hipMemsetAsync(d.sweep_ctr, 0xFF, 8, stream);
   if (e == hipSuccess) e = ec::launch_lattice(s->dev_d, d.n, k, a, stream);
   if (e == hipSuccess) e = ec::launch_zero_tallies(s->dev_d, d.C * d.C, stream);
-  if (e == hipSuccess) e = hipMemsetAsync(d.err, 0, 8, stream);
-  if (e == hipSuccess) e = hipMemsetAsync(d.dbg, 0, 8 * ec::kDebugWords, stream);
+  if (e == hipSuccess) e = hipMemsetAsync(d.status, 0, sizeof(ec::Status), stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.digest_ring, 0, 8 * ec::kDigestRing, stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.cell_digest, 0, 8 * (size_t)d.C * (size_t)d.C, stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.cell_done, 0, 8 * (size_t)d.C * (size_t)d.C, stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.queue, 0, 8, stream);
-  if (e == hipSuccess) e = hipMemsetAsync(d.ovl, 0, 32, stream);
   if (e == hipSuccess) e = hipMemsetAsync(d.gr_counts, 0, 8 * (size_t)(ec::kMaxGrBins + 1), stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);  // the host record is copied by now
   if (e != hipSuccess) {
@@ -621,14 +612,16 @@ ec_status ec_set_dep_wait_limit(ec_system s, double seconds) {
   return EC_OK;
 }
 
-static ec_status check_err(ec_system s) {
-  int32_t err[2] = {0, 0};
-  double dbg[ec::kDebugWords];
-  unsigned long long ovl[4] = {0, 0, 0, 0};
-  EC_HIP(s, hipMemcpyAsync(err, s->dev.err, 8, hipMemcpyDeviceToHost, s->stream));
-  EC_HIP(s, hipMemcpyAsync(dbg, s->dev.dbg, sizeof dbg, hipMemcpyDeviceToHost, s->stream));
-  EC_HIP(s, hipMemcpyAsync(ovl, s->dev.ovl, sizeof ovl, hipMemcpyDeviceToHost, s->stream));
+// Wait for the stream, read the system's status record (into *out if given)
+// and turn its device error word into a status.
+static ec_status check_err(ec_system s, ec::Status* out = nullptr) {
+  ec::Status st;
+  EC_HIP(s, hipMemcpyAsync(&st, s->dev.status, sizeof st, hipMemcpyDeviceToHost, s->stream));
   EC_HIP(s, hipStreamSynchronize(s->stream));
+  if (out) *out = st;
+  const int32_t* err = st.err;
+  const double* dbg = st.dbg;
+  const unsigned long long* ovl = st.ovl;
   if (err[0] == ec::ERR_OVERLAP) {
     char buf[256];
     std::snprintf(buf, sizeof buf,
@@ -660,10 +653,10 @@ static ec_status check_err(ec_system s) {
 ec_status ec_measure_pressure(ec_system s, double* z, double* bp, uint64_t* counts) {
   if (!s) return EC_E_INVALID;
   EC_HIP(s, ec::launch_reduce(s->dev_d, s->stream));
-  double red[8];
-  EC_HIP(s, hipMemcpyAsync(red, s->dev.red, sizeof red, hipMemcpyDeviceToHost, s->stream));
-  ec_status st = check_err(s);
+  ec::Status rec;
+  ec_status st = check_err(s, &rec);
   if (st != EC_OK) return st;
+  const double* red = rec.red;
   uint64_t cnt[ec::CNT_NCOL];
   for (int k = 0; k < ec::CNT_NCOL; ++k) std::memcpy(&cnt[k], &red[1 + k], 8);
   double chains = (double)cnt[ec::CNT_CHAINS];
@@ -684,13 +677,13 @@ ec_status ec_measure_psi6(ec_system s, double r_cut, double* psi_re, double* psi
     return EC_E_INVALID;
   }
   EC_HIP(s, ec::launch_psi6(s->dev_d, s->shape, rc, s->stream));
-  double red[3];
-  EC_HIP(s, hipMemcpyAsync(red, s->dev.psi_red, sizeof red, hipMemcpyDeviceToHost, s->stream));
   if (per_disk)
     EC_HIP(s, hipMemcpyAsync(per_disk, s->dev.psi, 16 * (size_t)s->p.n_disks, hipMemcpyDeviceToHost,
                              s->stream));
-  ec_status st = check_err(s);
+  ec::Status rec;
+  ec_status st = check_err(s, &rec);
   if (st != EC_OK) return st;
+  const double* red = rec.psi_red;
   if (psi_re) *psi_re = red[0];
   if (psi_im) *psi_im = red[1];
   if (mean_neighbours) *mean_neighbours = red[2];
@@ -708,18 +701,17 @@ ec_status ec_measure_psi6_delaunay(ec_system s, double r_search, double* psi_re,
     return EC_E_INVALID;
   }
   EC_HIP(s, ec::launch_psi6_delaunay(s->dev_d, s->shape, rs, s->stream));
-  double red[3];
-  unsigned long long bad[2];
-  EC_HIP(s, hipMemcpyAsync(red, s->dev.psi_red, sizeof red, hipMemcpyDeviceToHost, s->stream));
-  EC_HIP(s, hipMemcpyAsync(bad, s->dev.psi_err, sizeof bad, hipMemcpyDeviceToHost, s->stream));
   if (per_disk)
     EC_HIP(s, hipMemcpyAsync(per_disk, s->dev.psi, 16 * (size_t)s->p.n_disks, hipMemcpyDeviceToHost,
                              s->stream));
   if (neighbours)
     EC_HIP(s, hipMemcpyAsync(neighbours, s->dev.psi_nb, 4 * (size_t)s->p.n_disks,
                              hipMemcpyDeviceToHost, s->stream));
-  ec_status st = check_err(s);
+  ec::Status rec;
+  ec_status st = check_err(s, &rec);
   if (st != EC_OK) return st;
+  const double* red = rec.psi_red;
+  const unsigned long long* bad = rec.psi_err;
   if (bad[0] || bad[1]) {
     char buf[256];
     std::string why = "Delaunay neighbours not certified at r_search = ";
@@ -1337,9 +1329,7 @@ ec_status ec_sweep_static(const ec_params* p, double* x, double* y, int64_t firs
   d.y = y;
   d.psi = nullptr;
   d.psi_part = nullptr;
-  d.psi_red = nullptr;
   d.psi_nb = nullptr;
-  d.psi_err = nullptr;
   d.gr_counts = nullptr;
   d.obs_pos = nullptr;
   d.obs_id = nullptr;

@@ -73,6 +73,16 @@ constexpr int kRegions = 9;
 // Rejection variant: lifts of one chain that can be undone (LDS log entries).
 constexpr int kUndoCap = 256;
 
+// What the host reads back after a call, in one copy.
+struct Status {
+  int32_t err[2];                // device error word; number of chains that tripped a cap
+  double dbg[kDebugWords];       // state of the first wave that tripped a cap
+  unsigned long long ovl[4];     // overlap check: pairs found, first pair (i, j), its sweep
+  double red[8];                 // reduced tallies (contact sum, then the counters as bits)
+  double psi_red[3];             // Psi (re, im) and the mean neighbour count
+  unsigned long long psi_err[2]; // disks whose Voronoi cell was not certified; candidate overflows
+};
+
 // Everything a kernel needs: device pointers into the caller's workspace and
 // the derived constants.  Passed by value.
 struct Dev {
@@ -89,19 +99,17 @@ struct Dev {
   unsigned long long* digest_ring;  // [kDigestRing]
   unsigned long long* cell_digest;  // [C*C] digest of each cell in the last sweep it ran
   SweepDraws* draws;                // [1]
-  int32_t* err;                     // [1]
-  double* red;                      // [8]: reduced tallies (double sum + counters as bits)
+  int32_t* err;                     // (status->err)
+  Status* status;                   // [1] what the host reads after a call
   int32_t* chain_start;             // [max chains per sweep] start index within its cell
   double2* chain_dir;               // [max chains per sweep] direction of each chain
   int32_t* shuffle;                 // [N] rebin: places in the (cell, region) lists; then per-cell
                                     // shuffled lists (distinct-start mode)
-  double* dbg;                      // [kDebugWords] state of the first wave that tripped a cap
+  double* dbg;                      // (status->dbg)
   int64_t* sweep_ctr;               // [1] number of the current or last sweep, -1 before the first
   double2* psi;                     // [N] per-disk hexatic order Psi_k (re, im)
   double* psi_part;                 // [3 * ceil(N/256)] per-block sums (re, im, neighbours)
-  double* psi_red;                  // [3] Psi (re, im) and the mean neighbour count
   int32_t* psi_nb;                  // [N] Delaunay neighbour count of each disk
-  unsigned long long* psi_err;      // [2] disks whose Voronoi cell was not certified; candidate overflows
   double2* obs_pos;                 // [N] observables: positions grouped by the cells of their grid
   int32_t* obs_id;                  // [N] ids in that order
   int32_t* obs_list;                // [N] sorted places whose Delaunay neighbours need the wide search
@@ -111,7 +119,7 @@ struct Dev {
   unsigned long long* gr_counts;    // [kMaxGrBins + 1] pair counts per bin, then pairs < sigma
   int32_t* queue;                   // [1] ticket counter of the one-launch sweep
   int64_t* cell_done;               // [C*C] last sweep + 1 whose write-back the cell has published
-  unsigned long long* ovl;          // [4] overlap check: pairs found, first pair (i, j), its sweep
+  unsigned long long* ovl;          // (status->ovl)
 
   int64_t n;
   double sigma, sig2, ell, L, half_L, w, cap, b, inv_b;

@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(256) k_grid_clear(const Dev* __restrict__ ds, 
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i < ncell) d.obs_count[i] = 0;
   if (i < kObsCounters) d.obs_ctr[i] = 0;
-  if (i < 2) d.psi_err[i] = 0;
+  if (i < 2) d.status->psi_err[i] = 0;
 }
 
 __global__ void __launch_bounds__(256) k_grid_count(const Dev* __restrict__ ds, Grid g) {
@@ -240,9 +240,9 @@ __global__ void __launch_bounds__(1024) k_psi6_final(const Dev* __restrict__ ds,
   }
   if (t == 0) {
     const double n = (double)d.n;
-    d.psi_red[0] = sh[0][0] / n;
-    d.psi_red[1] = sh[1][0] / n;
-    d.psi_red[2] = sh[2][0] / n;
+    d.status->psi_red[0] = sh[0][0] / n;
+    d.status->psi_red[1] = sh[1][0] / n;
+    d.status->psi_red[2] = sh[2][0] / n;
   }
 }
 
@@ -420,13 +420,13 @@ __global__ void __launch_bounds__(256) k_delaunay_far(const Dev* __restrict__ ds
     long long fre = 0, fim = 0;
     int nb = 0;
     if (ncand > kMaxCand) {
-      if (lane == 0) atomicAdd(&d.psi_err[1], 1ull);
+      if (lane == 0) atomicAdd(&d.status->psi_err[1], 1ull);
     } else {
       bool e0 = false, e1 = false, o0 = false, o1 = false;
       long long r1 = 0, i1 = 0;
       if (lane < ncand) delaunay_edge(cand, ncand, lane, vmax2, e0, o0, fre, fim);
       if (lane + 64 < ncand) delaunay_edge(cand, ncand, lane + 64, vmax2, e1, o1, r1, i1);
-      if (__builtin_amdgcn_ballot_w64(o0 || o1) != 0 && lane == 0) atomicAdd(&d.psi_err[0], 1ull);
+      if (__builtin_amdgcn_ballot_w64(o0 || o1) != 0 && lane == 0) atomicAdd(&d.status->psi_err[0], 1ull);
       nb = __popcll(__builtin_amdgcn_ballot_w64(e0)) + __popcll(__builtin_amdgcn_ballot_w64(e1));
       fre = lanes_sum_i64<64>(fre + r1);
       fim = lanes_sum_i64<64>(fim + i1);
