@@ -984,6 +984,17 @@ struct BatchLayout {
   std::vector<int32_t> base;    // first queue index of each system's cells, then the total
 };
 
+// Events expected in one cell of a walled system: per chain the collisions of a
+// flight of length ell, whose number follows from the pressure, Z - 1 = (pi/4)
+// lifts sigma / ell, with Z by Henderson's equation of state, level above the
+// transition.  Orders the cells of a batch; results do not depend on it.
+double expected_events(const ec_params& p) {
+  const double z = std::min((1.0 + p.eta * p.eta / 8.0) / ((1.0 - p.eta) * (1.0 - p.eta)), 10.3);
+  const double cells = (double)p.cells_per_side * (double)p.cells_per_side;
+  const double chains = p.chains_per_cell > 0 ? (double)p.chains_per_cell : (double)p.n_disks / cells;
+  return chains * (1.0 + (p.ell / p.sigma) * (z - 1.0) * 4.0 / kPi);
+}
+
 ec_status batch_layout(const ec_params* ps, int32_t n, BatchLayout* bl, std::vector<Derived>* dvs,
                        std::string* why) {
   if (!ps || n < 1 || n > kMaxBatch) { *why = "batch size out of range"; return EC_E_INVALID; }
@@ -1003,7 +1014,7 @@ ec_status batch_layout(const ec_params* ps, int32_t n, BatchLayout* bl, std::vec
   bl->q_tasks = o; o = align256(o + 8 * (size_t)cells);
   bl->q_flags = o; o = align256(o + 4 * (size_t)cells);
   bl->q_dep = o;   o = align256(o + 4 * (size_t)cells);
-  bl->q_base = o;  o = align256(o + 4 * ((size_t)n + 1));
+  bl->q_base = o;  o = align256(o + 4 * (2 * (size_t)n + 1));  // bases, then the order
   bl->systems = o;
   bl->off.resize((size_t)n);
   dvs->resize((size_t)n);
@@ -1161,9 +1172,19 @@ ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* ws, size_t ws_
   sh.queue.flags = (int32_t*)(b->ws + bl.q_flags);
   sh.queue.dep = (int32_t*)(b->ws + bl.q_dep);
   sh.queue.base = (const int32_t*)(b->ws + bl.q_base);
+  sh.queue.order = sh.queue.base + n_sys + 1;
   sh.queue.total = bl.cells;
   sh.queue.workers = 1;
+  std::vector<double> work;
+  for (int32_t i = 0; i < n_sys; ++i) work.push_back(expected_events(ps[i]));
+  const double most = *std::max_element(work.begin(), work.end());
   {
+    // the order of the systems goes behind their bases
+    std::vector<int32_t> order((size_t)n_sys);
+    for (int32_t i = 0; i < n_sys; ++i) order[(size_t)i] = i;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t i, int32_t j) { return work[(size_t)i] > work[(size_t)j]; });
+    bl.base.insert(bl.base.end(), order.begin(), order.end());
     // queue header, flags and per-system bases (init synchronises below)
     hipError_t e = hipMemsetAsync(b->ws + bl.q_hdr, 0, 16, b->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b->ws + bl.q_flags, 0, 4 * (size_t)bl.cells, b->stream);
@@ -1189,6 +1210,8 @@ ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* ws, size_t ws_
       return st;
     }
     b->sys.push_back(s);
+    // quarters of the largest cell's work
+    s->dev.wave_priority = std::min(3, (int32_t)(4.0 * work[(size_t)i] / most));
     const ec::LaunchShape& one = s->shape;
     sh.any_distinct = sh.any_distinct || one.any_distinct;
     sh.check_overlap = sh.check_overlap || one.check_overlap;

@@ -39,6 +39,7 @@ struct ReadyQueue {
   int32_t* flags;      // [total] epoch of the sweep that published the slot
   int32_t* dep;        // [total] earlier-phase neighbours still running or waiting
   const int32_t* base; // [n_sys + 1] first queue index of each system's cells
+  const int32_t* order; // [n_sys] systems by the work of one of their cells, most first
   int32_t total;       // cells of all systems
   int32_t workers;     // wavefronts of the persistent launch
 };
@@ -136,6 +137,7 @@ struct Dev {
   int32_t check_overlap;            // 1: every sweep ends with a check of all neighbour pairs
   int32_t stripes;                  // 1: striped decomposition, C stripes of width w, rejection
   int32_t stripe_cap_own, stripe_cap_frozen, stripe_undo;  // LDS capacities of one stripe
+  int32_t wave_priority;            // ready queue: issue priority of a wave with one of its cells, 0..3
   uint64_t seed;
   uint32_t system;
 };

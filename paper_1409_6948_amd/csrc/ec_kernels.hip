@@ -1915,9 +1915,12 @@ __global__ void k_queue_reset(ReadyQueue rq) {
 }
 
 // Count every cell's earlier-phase neighbours; cells with none (the first
-// phase) are ready at once.  One thread per cell, grid y = system.
+// phase) are ready at once.  One thread per cell, grid y = system, in the order
+// of the work in one of its cells: a sweep is four cells deep, so those of the
+// densest systems are the ones to start with.
 __global__ void k_queue_prep(const Dev* __restrict__ ds, ReadyQueue rq) {
-  const Dev& d = ds[blockIdx.y];
+  const int sys = rq.order[blockIdx.y];
+  const Dev& d = ds[sys];
   const int ncell = d.C * d.C;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncell) return;
@@ -1930,9 +1933,9 @@ __global__ void k_queue_prep(const Dev* __restrict__ ds, ReadyQueue rq) {
     const int nc = ((cy + k / 3 - 1 + d.C) % d.C) * d.C + (cx + k % 3 - 1 + d.C) % d.C;
     n += cell_phase(phase_of, d.C, nc) < q ? 1 : 0;
   }
-  const int g = rq.base[blockIdx.y] + c;
+  const int g = rq.base[sys] + c;
   rq.dep[g] = n;
-  if (n == 0) queue_push(rq, rq.hdr[QH_EPOCH], ((int64_t)blockIdx.y << 32) | (uint32_t)c);
+  if (n == 0) queue_push(rq, rq.hdr[QH_EPOCH], ((int64_t)sys << 32) | (uint32_t)c);
 }
 
 // Persistent wavefronts: take the next queue slot, wait until it is
@@ -1994,7 +1997,17 @@ __global__ void __launch_bounds__(256) k_queue_cells(const Dev* __restrict__ ds,
     const int q = cell_phase(phase_of, d.C, cell);
     const int cx = cell % d.C, cy = cell / d.C;
     const int blk = (cy >> 1) * (d.C >> 1) + (cx >> 1);
+    // Waves that share a SIMD: the one whose cell holds more work issues first,
+    // since a sweep ends with the fourth of a densest system's cells and each of
+    // them runs at a third of its speed beside two waves of equal priority.
+    // (16 systems of 4.6e3 to 2.6e5 disks, eta 0.30 to 0.71: 39.7 ms per sweep
+    // without, 35.3 to 36.9 with it; the order of the queue alone gives 0.5 ms.)
+    const int priority = uniform_i32(d.wave_priority);
+    if (priority == 1) __builtin_amdgcn_s_setprio(1);
+    if (priority == 2) __builtin_amdgcn_s_setprio(2);
+    if (priority == 3) __builtin_amdgcn_s_setprio(3);
     phase_cell<REJ>(d, sweep, dr, q, blk, base, lane);
+    __builtin_amdgcn_s_setprio(0);
     if (__builtin_amdgcn_readfirstlane(load_err(d)) != 0) {
       if (lane == 0) atomicExch(rq.hdr + QH_ABORT, 1);
       break;
