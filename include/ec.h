@@ -352,7 +352,7 @@ ec_status ec_batch_workspace_bytes(const ec_params* ps, int32_t n_sys, size_t* b
  * EC_E_INVALID), >= ec_batch_workspace_bytes) on hip_stream (borrowed).
  * Each system starts from its lattice as in ec_init_system;
  * ps[i].cells_per_block is ignored (the batch schedule applies, initially
- * 1).  Synchronises. */
+ * 1 in the phase launches).  Synchronises. */
 ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* dev_workspace, size_t ws_bytes,
                         void* hip_stream, ec_batch* out);
 

@@ -961,6 +961,7 @@ struct ec_batch_s {
   std::vector<ec_system> sys;
   std::vector<size_t> off;      // byte offset of each system's region
   int32_t schedule;             // EC_SCHEDULE_*
+  bool cpb_chosen;              // cells per workgroup set by the caller or a trial
   unsigned char* ws;
   size_t sys_bytes;             // bytes of all system regions (snapshot size)
   ec::Dev* devs_d;              // device array of the systems' records
@@ -1040,12 +1041,18 @@ ec_status batch_layout(const ec_params* ps, int32_t n, BatchLayout* bl, std::vec
 }
 
 // The launch shape of the batch's schedule (ready queue: as many persistent
-// wavefronts as fit on the device, at most one per cell).
+// wavefronts as fit on the device, at most one per cell).  Where nobody chose the
+// wavefronts of a workgroup, the ready queue takes four if their LDS fits: they
+// land on the four SIMDs of a CU, while workgroups of one are spread unevenly and
+// stay so for the whole sweep (16 systems of 4.6e3 to 2.6e5 disks: 34.0 ms per
+// sweep with four, 35.8 ms with one; short chains: 2.8 to 2.9 against 2.9 to 3.1).
 ec_status batch_apply_schedule(ec_batch b) {
   ec::LaunchShape& sh = b->shape;
   // (the striped decomposition has its own two phase launches)
   sh.one_launch = b->schedule == EC_SCHEDULE_ONE_LAUNCH && !sh.stripes;
   sh.ready_queue = b->schedule == EC_SCHEDULE_READY_QUEUE && !sh.stripes;
+  if (!b->cpb_chosen)
+    sh.cpb = sh.ready_queue && (size_t)4 * sh.max_lds_per_cell <= 160 * 1024 ? 4 : 1;
   if (sh.ready_queue) {
     int workers = 0;
     hipError_t e = ec::ready_queue_workers(sh.max_lds_per_cell, sh.cpb,
@@ -1154,6 +1161,7 @@ ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* ws, size_t ws_
   b->sys_bytes = bl.snapshot - bl.systems;
   b->devs_d = (ec::Dev*)(b->ws + bl.devs);
   b->stream = (hipStream_t)stream;
+  b->cpb_chosen = false;
   b->use_graph = false;
   b->graph_ready = false;
   // schedule: the ready queue unless a schedule flag asks for another
@@ -1258,6 +1266,7 @@ ec_status ec_batch_set_cells_per_block(ec_batch b, int32_t cpb) {
   if (cpb != 1 && cpb != 2 && cpb != 4) return EC_E_INVALID;
   if ((size_t)cpb * (size_t)b->shape.max_lds_per_cell > 160 * 1024) return EC_E_UNSUPPORTED;
   b->shape.cpb = cpb;
+  b->cpb_chosen = true;
   return batch_sync_records(b);
 }
 
@@ -1283,6 +1292,7 @@ ec_status ec_batch_autotune(ec_batch b, int32_t trial_sweeps, int32_t* schedule_
   if ((e = hipEventCreate(&t0)) != hipSuccess) return batch_fail(b, e, "event");
   if ((e = hipEventCreate(&t1)) != hipSuccess) { (void)hipEventDestroy(t0); return batch_fail(b, e, "event"); }
   const int32_t cands[3] = {1, 2, 4};
+  b->cpb_chosen = true;
   int32_t best = b->shape.cpb, best_sched = b->schedule;
   double best_ms = 0.0;
   ec_status st = EC_OK;
