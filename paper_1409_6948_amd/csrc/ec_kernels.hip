@@ -9,7 +9,7 @@
 // cell's own disks and its frozen neighbours (centres within sigma outside
 // the cell) are staged in LDS in a grid of square bins of side b <
 // sigma/sqrt(2); such a bin holds at most one centre of a configuration
-// without overlaps, so one slot per bin suffices and a cell takes about 19 KB
+// without overlaps, so one slot per bin suffices and a cell takes about 18 KB
 // (eight cells, two wavefronts per SIMD, per CU).  One event search reads an
 // 8 x 8 window of bins around the moving disk, one slot per lane, computes
 // the contact distance of every slot in FP64, and takes a wave-wide minimum
