@@ -993,7 +993,7 @@ double expected_events(const ec_params& p) {
   const double z = std::min((1.0 + p.eta * p.eta / 8.0) / ((1.0 - p.eta) * (1.0 - p.eta)), 10.3);
   const double cells = (double)p.cells_per_side * (double)p.cells_per_side;
   const double chains = p.chains_per_cell > 0 ? (double)p.chains_per_cell : (double)p.n_disks / cells;
-  return chains * (1.0 + (p.ell / p.sigma) * (z - 1.0) * 4.0 / kPi);
+  return std::min(chains * (1.0 + (p.ell / p.sigma) * (z - 1.0) * 4.0 / kPi), 1e30);
 }
 
 ec_status batch_layout(const ec_params* ps, int32_t n, BatchLayout* bl, std::vector<Derived>* dvs,
