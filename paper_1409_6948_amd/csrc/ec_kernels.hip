@@ -758,7 +758,9 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // Registers are fixed: halves of a pair cannot be named otherwise.  Wait states
 // kept: 2 from a vector write to its use by a DPP step, or of a scalar or vcc to
 // a vector use; 1 to a lane read, or from a root or reciprocal estimate to its
-// use.  Everything read from LDS has arrived where the code is left.
+// use.  Everything read from LDS has arrived where the code is left.  Every
+// output is written before the last input has been read, so all are early
+// clobbers: without that an input that dies here may be given v96, v97 or v120.
 //
 // Costs found by doubling single instructions and by adding idle ones (a
 // wavefront alone on its SIMD): vector and scalar instructions 4 cycles, an LDS
@@ -1056,20 +1058,20 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
       EC_FOUR(, , EC_READ_WINDOW, LOG, STEP, FROZEN)                                           \
       REFLECTION                                                                               \
       EC_LEAVE                                                                                 \
-      : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(widx), "+{v[70:71]}"(ax),             \
-        "+{v[72:73]}"(ay), "+{s[90:91]}"(nrem), "+{s[92:93]}"(dacc), "+{v[78:79]}"(sum),       \
-        "+{v[80:81]}"(dx), "+{v[82:83]}"(dy), "+{v[84:85]}"(guard), "+{v94}"(rec_lo),          \
-        "+{v95}"(rec_hi), "+{v98}"(m), "+{v99}"(rec_tag), "={v[96:97]}"(s), "={v120}"(key),    \
-        [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+s"(a_slot),                      \
-        [a_lidx] "+s"(a_lidx), "+{m0}"(n_ring), [offx] "+s"(offx), [offy] "+s"(offy),    \
-        [n_frozen] "+s"(n_frozen), [woff] "+v"(woff), [mask] "=&s"(a_mask), [t] "=&s"(a_t),    \
+      : "+&{v[64:65]}"(p.x), "+&{v[66:67]}"(p.y), "+&{v69}"(widx), "+&{v[70:71]}"(ax),         \
+        "+&{v[72:73]}"(ay), "+&{s[90:91]}"(nrem), "+&{s[92:93]}"(dacc), "+&{v[78:79]}"(sum),   \
+        "+&{v[80:81]}"(dx), "+&{v[82:83]}"(dy), "+&{v[84:85]}"(guard), "+&{v94}"(rec_lo),      \
+        "+&{v95}"(rec_hi), "+&{v98}"(m), "+&{v99}"(rec_tag), "=&{v[96:97]}"(s), "=&{v120}"(key), \
+        [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+&s"(a_slot),                     \
+        [a_lidx] "+&s"(a_lidx), "+&{m0}"(n_ring), [offx] "+&s"(offx), [offy] "+&s"(offy),      \
+        [n_frozen] "+&s"(n_frozen), [woff] "+&v"(woff), [mask] "=&s"(a_mask), [t] "=&s"(a_t),  \
         [u] "=&s"(a_u), [next] "=&s"(a_next), [slo] "=&s"(a_slo), [shi] "=&s"(a_shi),          \
         [expect] "=&s"(a_expect) UNDO                                                          \
       : [pos] "v"(pos_at), [meta] "v"(meta_at), [own_loc] "v"(own_loc_at), [loff] "v"(loff),   \
         [mid] "s"(mid), [inner] "s"(inner), [sig2] "s"(s_sig2), [inv_b] "s"(s_inv_b),          \
         [reach] "s"(s_reach), [gridb] "s"(s_gridb), [inv_g32] "s"(s_inv_g32),                  \
         [top] "s"(s_top), [limit] "s"(limit), [low31] "s"(0x7FFFFFFF)                          \
-      : "vcc", "scc", "memory", "s94", "s95", "s96", "s97", "s98", "s99", "v100",        \
+      : "vcc", "scc", "memory", "s94", "s95", "s96", "s97", "s98", "s99", "v100",              \
         "v101", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v109", "v110",        \
         "v111", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v121",        \
         "v122", "v123", "v124", "v125", "v126", "v127")
@@ -1083,7 +1085,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 #define EC_UNDO_STEP                                                                           \
   EC_W("v_add_u32_e32 %[uslot], 8, %[uslot]")                                                  \
   EC_W("v_add_u32_e32 %[upos], 16, %[upos]")
-#define EC_UNDO_OPERANDS , [uslot] "+v"(uslot_at), [upos] "+v"(upos_at)
+#define EC_UNDO_OPERANDS , [uslot] "+&v"(uslot_at), [upos] "+&v"(upos_at)
 
 // One periodic cell: the window wraps around the box (an index i in [-nb, 2 nb)
 // is brought into [0, nb) as the least of i and i + nb, then of i and i - nb,
@@ -1128,11 +1130,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   asm volatile(                                                                                \
       EC_FOUR(EC_NEAREST_IMAGE, EC_TERM_IMAGE, EC_READ_PERIODIC, , , "2f")                     \
       EC_LEAVE                                                                                 \
-      : "+{v[64:65]}"(p.x), "+{v[66:67]}"(p.y), "+{v69}"(wsl), "+{v[70:71]}"(ax),              \
-        "+{v[72:73]}"(ay), "+{s[90:91]}"(nrem), "+{s[92:93]}"(dacc), "+{v[78:79]}"(acc),       \
-        "+{v94}"(rec_lo), "+{v95}"(rec_hi), "+{v98}"(m), "+{v99}"(rec_tag), "={v[96:97]}"(s),  \
-        "={v120}"(key), [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+s"(a_slot),      \
-        [a_lidx] "+s"(a), "+{m0}"(n_ring), [mask] "=&s"(a_mask), [t] "=&s"(a_t),               \
+      : "+&{v[64:65]}"(p.x), "+&{v[66:67]}"(p.y), "+&{v69}"(wsl), "+&{v[70:71]}"(ax),          \
+        "+&{v[72:73]}"(ay), "+&{s[90:91]}"(nrem), "+&{s[92:93]}"(dacc), "+&{v[78:79]}"(acc),   \
+        "+&{v94}"(rec_lo), "+&{v95}"(rec_hi), "+&{v98}"(m), "+&{v99}"(rec_tag), "=&{v[96:97]}"(s), \
+        "=&{v120}"(key), [kmin] "=&s"(key_min), [full] "=&s"(full), [a_slot] "+&s"(a_slot),    \
+        [a_lidx] "+&s"(a), "+&{m0}"(n_ring), [mask] "=&s"(a_mask), [t] "=&s"(a_t),             \
         [u] "=&s"(a_u), [next] "=&s"(a_next), [slo] "=&s"(a_slo), [shi] "=&s"(a_shi),          \
         [expect] "=&s"(a_expect)                                                               \
       : "{v[80:81]}"(dx), "{v[82:83]}"(dy), "{v[84:85]}"(guard), [pos] "v"(pos_at),            \
