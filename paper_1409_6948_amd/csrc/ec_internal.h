@@ -169,6 +169,17 @@ __host__ __device__ inline CellLds cell_lds_layout(int gridb, int cap_own, bool 
   return l;
 }
 
+// A walled cell's disk k still has its slot: the slot that own_loc names for it
+// names it (its meta word) and holds a centre (x is a coordinate; NaN where
+// empty).  Stores of a moved centre go unchecked to the bin it lies in; where
+// that held another disk (possible only if disks overlap), no later move leaves
+// every disk of the cell with its slot, since the disks are then more than the
+// slots that hold a centre.  An undo can, but one of its moves then starts from
+// a slot that is empty.
+__host__ __device__ inline bool slot_kept(uint32_t meta_word, uint32_t k, double x) {
+  return meta_word == k && x == x;
+}
+
 // LDS of the binned periodic cell: pbins x pbins slots (FP64 position, 32-bit
 // disk id), the slot of every disk, the shuffled start list, one sink slot
 // per lane.

@@ -1610,9 +1610,11 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
         // slot it left (a slot vacated in between was refilled only by moves
         // that are undone before it) and to its old position
         if (lane == 0) {
+          bool lost = false;  // the slot to leave is empty already: another disk's undo left it
           for (int u = n_undo - 1; u >= 0; --u) {
             const int2 sl = undo_slot[u];
             const double2 old = undo_pos[u];
+            lost |= __builtin_isnan(pos[sl.y].x);
             if (sl.y != sl.x) {
               const uint32_t mv = meta[sl.y];
               pos[sl.y] = nan2;
@@ -1621,6 +1623,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
             }
             pos[sl.x] = old;
           }
+          if (lost) atomicOr(d.err, ERR_BIN_CAP);
         }
         n_undo = 0;
         if (kind == EV_FROZEN) n_frozen += 1;
@@ -1718,8 +1721,27 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
 #undef EC_SET_DIRECTION
   }
 
-  // ---- write back: old position + local displacement, wrapped --------------
+  // ---- does every disk have its slot? --------------------------------------
+  // The written-out loop and the short way to the chain end store into the bin
+  // of the moved centre without looking whether it is empty.  It is, unless
+  // disks overlapped.  One look per disk and sweep here, where one per event
+  // would cost a trip to LDS and a branch each.  (An undo looks for itself: it
+  // can give a lost disk back under another's name.)  If not, the cell is left
+  // as it was before the phase.
   wave_sync();
+  {
+    bool lost = false;
+    for (int k = lane; k < n_own; k += 64) {
+      const int at = (int)own_loc[k];
+      lost |= !slot_kept(meta[at], (uint32_t)k, pos[at].x);
+    }
+    if (__builtin_amdgcn_ballot_w64(lost) != 0) {
+      if (lane == 0) atomicOr(d.err, ERR_BIN_CAP);
+      return;
+    }
+  }
+
+  // ---- write back: old position + local displacement, wrapped --------------
   uint32_t last_lifts;
   h ^= digest_records(rec_lo, rec_hi, rec_tag, lane, n_ring, ring_first, own_gid, last_lifts);
   if (REJ == 0) n_lift += last_lifts;
