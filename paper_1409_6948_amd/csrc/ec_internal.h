@@ -60,6 +60,18 @@ constexpr int kMaxDrawTries = 256;
 constexpr int kDebugWords = 16;
 
 constexpr int kDigestRing = 1024;
+// Workgroups of the pair histogram over n disks, r_max in units of sigma: 1024 (each
+// adds all its bins to the global counts at the end), or as many as 256 disks each
+// need, but so many that no 32-bit bin of a workgroup can overflow.  A pair adds 2,
+// in the workgroup of one of its disks, and at most (2 pi / sqrt 3) u^2 + pi u other
+// disks lie within u diameters of one (Oler's bound for a disc).
+__host__ __device__ inline int64_t histogram_groups(int64_t n, double r_max) {
+  const int64_t blocks = (n + 255) / 256;
+  const double per_block = 256.0 * 2.0 * (3.6276 * r_max * r_max + 3.1416 * r_max);
+  const int64_t most = per_block < 4294967295.0 ? (int64_t)(4294967295.0 / per_block) : 1;  // blocks of one workgroup
+  const int64_t least = (blocks + most - 1) / most, wanted = blocks < 1024 ? blocks : 1024;
+  return least > wanted ? least : wanted;
+}
 // Counters of the observables' grid: places of the sorted arrays taken, disks
 // on the Delaunay list.
 enum { OBS_CURSOR = 0, OBS_LISTED = 1, kObsCounters = 2 };

@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(256) k_delaunay_far(const Dev* __restrict__ ds
 // together.  Counts go to a histogram per workgroup in LDS, then to the global
 // one (integers: exact and independent of order); the workgroups go over the
 // disks in strides, since each adds all its bins to the global counts at the
-// end.  Pairs closer than sigma are counted apart.  36 us for 303k disks in
+// end (how many there are: histogram_groups).  Pairs closer than sigma are counted apart.  36 us for 303k disks in
 // random order (r_max 1.5, 500 bins), the grid before it 41 us; 12.2 ms as a
 // scan of the simulation cells.
 // ---------------------------------------------------------------------------
@@ -612,11 +612,11 @@ hipError_t launch_psi6_delaunay(const Dev* ds, const LaunchShape& sh, double r_s
 
 hipError_t launch_gr(const Dev* ds, const LaunchShape& sh, double r_max, double delta, int n_bins,
                      hipStream_t st) {
-  const unsigned nblk = (unsigned)((sh.max_n + 255) / 256);
   const Grid g = grid_for(sh, r_max);
   hipError_t e = launch_grid(ds, sh, g, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gr, dim3(nblk < 1024 ? nblk : 1024, 1), dim3(256), 0, st, ds, g, r_max, delta, n_bins);
+  hipLaunchKernelGGL(k_gr, dim3((unsigned)histogram_groups(sh.max_n, r_max / sh.sigma), 1), dim3(256), 0, st, ds, g,
+                     r_max, delta, n_bins);
   return hipGetLastError();
 }
 
