@@ -144,18 +144,17 @@ __device__ __forceinline__ void store_psi(const Dev& d, int id, long long fre, l
 // ---------------------------------------------------------------------------
 // Hexatic order parameter (Sec. 2, eq. Psi) with cutoff neighbours.  One
 // thread per disk in sorted order (the lanes of a wave then read the same
-// cells) tests the disks of 3 x 3 grid cells of side >= r_cut.  The neighbours
-// found are put aside in LDS and their bond terms, two divisions each, taken
-// together afterwards: of about 16 disks tested 6 are neighbours, and each
-// lane's 6 come at other places of its scan.  Bound by instruction issue (about
-// 20 B per disk are read and written): 71 us for 1.2M disks at eta 0.72, the
-// grid before it 55 us; 6.3 ms as a scan of the simulation cells of 290 disks.
+// cells) tests the disks of 3 x 3 grid cells of side >= r_cut, of which about a
+// third are neighbours whatever r_cut is, and takes a neighbour's bond term at
+// once.  (With the terms put aside in LDS, eight to a lane, a lane whose eight
+// are full makes the wave wait for it alone: 0.74 against 0.31 ms for 65k disks
+// at eta 0.05 and r_cut 31.7, and nothing gained at short range: 72 against 74
+// us for 1.2M disks at eta 0.72 and r_cut 1.4.)  Bound by instruction issue
+// (about 20 B per disk are read and written); the grid before it 55 us; 6.3 ms
+// as a scan of the simulation cells of 290 disks.
 // ---------------------------------------------------------------------------
-constexpr int kStash = 8;
-
 __global__ void __launch_bounds__(256) k_psi6(const Dev* __restrict__ ds, Grid g, double rc2) {
   const Dev& d = ds[blockIdx.y];
-  __shared__ double2 stash[kStash][256];
   const int t = (int)threadIdx.x;
   const int64_t i = (int64_t)blockIdx.x * 256 + t;
   if (i >= d.n) return;
@@ -164,27 +163,21 @@ __global__ void __launch_bounds__(256) k_psi6(const Dev* __restrict__ ds, Grid g
   int2 r[9];
   grid_block(d, g, p, r);
   long long fre = 0, fim = 0;
-  int nb = 0, held = 0;
-  auto flush = [&]() {
-    for (int k = 0; k < held; ++k) {
-      const double2 o = stash[k][t];
-      bond6(o.x, o.y, o.x * o.x + o.y * o.y, fre, fim);
-    }
-    nb += held;
-    held = 0;
-  };
+  int nb = 0;
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
+    double2 next = p;
+    if (r[k].x < r[k].y) next = d.obs_pos[r[k].x];
     for (int j = r[k].x; j < r[k].y; ++j) {
-      if (j == i) continue;
-      const double2 o = offset_to(d.obs_pos[j], p, L, half_L);
-      if (o.x * o.x + o.y * o.y < rc2) {
-        stash[held][t] = o;
-        if (++held == kStash) flush();
+      const double2 o = offset_to(next, p, L, half_L);
+      next = d.obs_pos[j + 1 < r[k].y ? j + 1 : j];  // in flight while this one is tested
+      const double r2 = o.x * o.x + o.y * o.y;
+      if (j != i && r2 < rc2) {
+        bond6(o.x, o.y, r2, fre, fim);
+        nb += 1;
       }
     }
   }
-  flush();
   store_psi(d, d.obs_id[i], fre, fim, nb);
 }
 
@@ -440,20 +433,19 @@ __global__ void __launch_bounds__(256) k_delaunay_far(const Dev* __restrict__ ds
 // per disk in sorted order tests the disks of 3 x 3 grid cells of side >=
 // r_max, minimum image, bin = floor((sqrt(dx*dx + dy*dy) - sigma) / delta).
 // A pair counts twice (it is ordered) and is looked at once, from the disk of
-// the lower sorted place; |offset| is the same number from either disk.  As in
-// k_psi6 the pairs found are put aside and their roots and divisions taken
-// together.  Counts go to a histogram per workgroup in LDS, then to the global
-// one (integers: exact and independent of order); the workgroups go over the
-// disks in strides, since each adds all its bins to the global counts at the
-// end (how many there are: histogram_groups).  Pairs closer than sigma are counted apart.  36 us for 303k disks in
-// random order (r_max 1.5, 500 bins), the grid before it 41 us; 12.2 ms as a
-// scan of the simulation cells.
+// the lower sorted place; |offset| is the same number from either disk.  Counts
+// go to a histogram per workgroup in LDS, then to the global one (integers:
+// exact and independent of order); the workgroups go over the disks in strides,
+// since each adds all its bins to the global counts at the end (how many there
+// are: histogram_groups).  Pairs closer than sigma are counted apart.  35 us for
+// 303k disks in random order (r_max 1.5, 500 bins), the grid before it 41 us;
+// 12.2 ms as a scan of the simulation cells.  (As in k_psi6 nothing is put aside:
+// 16k disks at eta 0.7, r_max 33.9, 2.6 ms against 10.3 ms.)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_gr(const Dev* __restrict__ ds, Grid g, double r_max, double delta,
                                             int n_bins) {
   const Dev& d = ds[blockIdx.y];
   __shared__ unsigned int hist[kMaxGrBins + 1];
-  __shared__ double stash[kStash][256];
   const int t = (int)threadIdx.x;
   for (int i = t; i <= n_bins; i += 256) hist[i] = 0;
   __syncthreads();
@@ -462,29 +454,23 @@ __global__ void __launch_bounds__(256) k_gr(const Dev* __restrict__ ds, Grid g, 
     const double2 p = d.obs_pos[i];
     int2 r[9];
     grid_block(d, g, p, r);
-    int held = 0;
-    auto flush = [&]() {
-      for (int k = 0; k < held; ++k) {
-        const double dist = sqrt(stash[k][t]);
-        const double b = floor((dist - sigma) / delta);
-        if (dist < sigma) atomicAdd(&hist[n_bins], 2u);
-        else if (b < (double)n_bins) atomicAdd(&hist[(int)b], 2u);
-      }
-      held = 0;
-    };
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      for (int j = r[k].x; j < r[k].y; ++j) {
-        if (j <= i) continue;
-        const double2 o = offset_to(d.obs_pos[j], p, L, half_L);
+      const int first = r[k].x > i ? r[k].x : (int)i + 1;
+      double2 next = p;
+      if (first < r[k].y) next = d.obs_pos[first];
+      for (int j = first; j < r[k].y; ++j) {
+        const double2 o = offset_to(next, p, L, half_L);
+        next = d.obs_pos[j + 1 < r[k].y ? j + 1 : j];  // in flight while this one is tested
         const double d2 = o.x * o.x + o.y * o.y;
         if (d2 < r2max) {
-          stash[held][t] = d2;
-          if (++held == kStash) flush();
+          const double dist = sqrt(d2);
+          const double b = floor((dist - sigma) / delta);
+          if (dist < sigma) atomicAdd(&hist[n_bins], 2u);
+          else if (b < (double)n_bins) atomicAdd(&hist[(int)b], 2u);
         }
       }
     }
-    flush();
   }
   __syncthreads();
   for (int i = t; i <= n_bins; i += 256)
