@@ -582,7 +582,10 @@ hipError_t launch_psi6_delaunay(const Dev* ds, const LaunchShape& sh, double r_s
   // (Oler's bound for a disc), which only the second pass would notice.
   const double near = 2.0 * sh.box / sqrt((double)sh.max_n), u = r_search / sh.sigma;
   const bool two = near < r_search && 3.6276 * u * u + 3.1416 * u + 1.0 <= (double)kMaxCand;
-  const Grid g = grid_for(sh, near < r_search ? near : r_search);
+  // Where all disks take the wide search, the grid is as wide as that: 9 cells
+  // instead of 25 or more of the first pass's width with four disks each for a
+  // wavefront to test (1M disks, eta 0.1, r_search 6: 2.3 against 4.0 ms).
+  const Grid g = grid_for(sh, two ? near : r_search);
   hipError_t e = launch_grid(ds, sh, g, st);
   if (e != hipSuccess) return e;
   if (two)
