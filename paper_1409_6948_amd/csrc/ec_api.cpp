@@ -1042,21 +1042,22 @@ ec_status batch_layout(const ec_params* ps, int32_t n, BatchLayout* bl, std::vec
 
 // The launch shape of the batch's schedule (ready queue: as many persistent
 // wavefronts as fit on the device, at most one per cell).  Where nobody chose the
-// wavefronts of a workgroup, the ready queue takes four if their LDS fits: they
-// land on the four SIMDs of a CU, while workgroups of one are spread unevenly and
-// stay so for the whole sweep (16 systems of 4.6e3 to 2.6e5 disks: 34.0 ms per
-// sweep with four, 35.8 ms with one; short chains: 2.8 to 2.9 against 2.9 to 3.1).
+// wavefronts of a workgroup, the ready queue takes queue_cells_per_block's.
 ec_status batch_apply_schedule(ec_batch b) {
   ec::LaunchShape& sh = b->shape;
   // (the striped decomposition has its own two phase launches)
   sh.one_launch = b->schedule == EC_SCHEDULE_ONE_LAUNCH && !sh.stripes;
   sh.ready_queue = b->schedule == EC_SCHEDULE_READY_QUEUE && !sh.stripes;
-  if (!b->cpb_chosen)
-    sh.cpb = sh.ready_queue && (size_t)4 * sh.max_lds_per_cell <= 160 * 1024 ? 4 : 1;
+  if (!b->cpb_chosen) sh.cpb = 1;
   if (sh.ready_queue) {
-    int workers = 0;
-    hipError_t e = ec::ready_queue_workers(sh.max_lds_per_cell, sh.cpb,
-                                           sh.reject ? 1 : 0, &workers);
+    const int rej = sh.reject ? 1 : 0;
+    int workers = 0, four = 0;
+    hipError_t e = ec::ready_queue_workers(sh.max_lds_per_cell, sh.cpb, rej, &workers);
+    if (e == hipSuccess && !b->cpb_chosen && (size_t)4 * sh.max_lds_per_cell <= 160 * 1024) {
+      e = ec::ready_queue_workers(sh.max_lds_per_cell, 4, rej, &four);
+      sh.cpb = ec::queue_cells_per_block(workers, four);
+      if (sh.cpb == 4) workers = four;
+    }
     if (e != hipSuccess) {
       b->last_error = std::string("ready-queue occupancy: ") + hipGetErrorString(e);
       return EC_E_HIP;

@@ -263,6 +263,16 @@ hipError_t launch_sweep(const Dev* ds, const LaunchShape& sh, hipStream_t st,
 hipError_t launch_reduce(const Dev* ds, hipStream_t st);
 // Allow the phase kernel up to `bytes` of dynamic LDS per workgroup.
 hipError_t set_phase_lds_limit(int bytes);
+// Wavefronts per workgroup of the ready queue, from the wavefronts that fit on the
+// device with one each and with four (0: four do not fit).  Four land on the four
+// SIMDs of a CU, while workgroups of one are spread unevenly and stay so for the
+// whole sweep: 16 systems of 64 disks per cell (12 KB of LDS, 12 wavefronts per CU
+// either way) 34.0 against 35.8 ms per sweep, 64 systems of 160 (33 KB, 4 either
+// way) 57.3 against 60.3.  But four are never worth a wavefront that fits no more:
+// 64 systems of 96 disks per cell (21 KB, 4 per CU against 7) 57.9 against 42.2, of
+// 128 (27 KB, 4 against 6) 57.1 against 46.3; rejected short chains of 96 (29 KB, 4
+// against 5) 5.6 against 4.8.
+inline int queue_cells_per_block(int one, int four) { return four >= one ? 4 : 1; }
 // Wavefronts of the ready-queue launch that fit on the device at once with
 // this much LDS per cell and cells per workgroup (resident workgroups per CU
 // times CUs times cells per workgroup).
