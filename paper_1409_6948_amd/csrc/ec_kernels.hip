@@ -1349,7 +1349,7 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
   const double s_sig2 = readlane_f64(sig2, 0), s_inv_b = readlane_f64(inv_b, 0);
   const double s_reach = readlane_f64(reach * (1.0 - 0x1p-20), 0);
   const int s_gridb = uniform_i32(gridb), s_inv_g32 = uniform_i32((int)inv_g32), s_top = uniform_i32(nb - 6);
-  const bool use_window = d.search == 0;
+  const int use_window = uniform_i32(d.search == 0 ? 1 : 0);
   const uint64_t wall_x_id = (uint64_t)d.n, wall_y_id = (uint64_t)d.n + 1, end_id = (uint64_t)d.n + 3;
   int aborted = 0;
   int stop = 0;  // nonzero once a poll sees the device error word set
@@ -1437,8 +1437,12 @@ __device__ __forceinline__ void phase_cell(const Dev& d, const int64_t sweep, co
       // (all ones: no contact) and the wave minimum of those
       double s;
       uint32_t key, key_min;
-      // plain lifts and reflections, up to the next digest of 64 records
-      for (;;) {
+      // plain lifts and reflections, up to the next digest of 64 records (none
+      // where no window is to vouch for a move: every event is then the exact
+      // search's, below)
+      s = 0.0;
+      key = key_min = 0xFFFFFFFFu;
+      while (use_window != 0) {
         const int before = n_ring;
         double sum = REJ == 1 ? chain_acc : acc, dacc = 0.0;
         int limit = kDigestBatch, full, a_t, a_u, a_next, a_slo, a_shi, a_expect, woff = loff + offx;
