@@ -188,13 +188,13 @@ def main():
                          "(one launch for a system alone, a ready queue for a batch)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--precision", choices=("fp64", "fp32-screen"), default=None,
-                    help="fp32-screen: FP32 screening of candidates, FP64 for the survivors "
-                         "and every commit (identical events); default: the workload's own "
-                         "(FP64 for pec_1m, FP32 screen for pec_16m and batch64)")
+                    help="fp32-screen is an alias of fp64 (the same kernel); default: the "
+                         "value the workload names (fp64 for pec_1m, fp32-screen for pec_16m "
+                         "and batch64)")
     ap.add_argument("--other-precision", action="store_true",
-                    help="walled cells: also run the same sweeps from the same start in the "
-                         "other precision (FP64 or FP32 screen), compare the per-sweep digests "
-                         "and report its time")
+                    help="walled cells: run the same sweeps from the same start once more, under "
+                         "the other value of --precision (the same kernel), and compare the "
+                         "per-sweep digests: whether a run repeats bit for bit")
     ap.add_argument("--copy-probe-mb", type=int, default=0,
                     help="run one device-to-device copy of this many MiB first (a kernel of "
                          "known traffic for scaling hardware byte counters)")
@@ -354,8 +354,9 @@ def main():
         "rebin": rebin,
     }
     if w["cells"] > 1 and args.other_precision and digests is not None:
-        # the same sweeps from the same start in the other form; identical
-        # collision sequences give identical per-sweep digests
+        # the same sweeps from the same start once more (both values of the
+        # precision run one kernel): identical collision sequences give identical
+        # per-sweep digests
         g.close()
         other = "fp64" if precision == "fp32-screen" else "fp32-screen"
         po = P.make_params(w["n"], w["eta"], w["ell"], w["cells"], dir_mode=w["dir_mode"],
@@ -381,8 +382,8 @@ def main():
             "precision": other, "ms_per_step": ms_o,
             "value": counts_o["lifts"] / (ms_o * args.steps / 1e3),
             "sweeps_compared": args.warmup + args.steps,
-            "digests_identical": bool(np.array_equal(digests, dig_o)),
-            "speedup_of_this_precision": ms_o / (gpu_ms / args.steps)}
+            "same_kernel": True,
+            "digests_identical": bool(np.array_equal(digests, dig_o))}
     if not args.no_cpu_baseline:
         print("# CPU oracle baseline (phase-parallel)", file=sys.stderr, flush=True)
         line["cpu_baseline"] = cpu_baseline(w)
@@ -421,10 +422,10 @@ def _batch_run(P, torch, ps, args, schedule_tune=True):
 
 
 def bench_batch(args, torch, P):
-    """Aggregate lifts/s of the 64-system ensemble in the batched form, in the
-    requested precision (default: FP32 screening with FP64 commits), the same
-    sweeps in the other precision (digests compared system by system), and the
-    same sweeps run system by system (solo launches, one after another)."""
+    """Aggregate lifts/s of the 64-system ensemble in the batched form, the same
+    sweeps once more under the other value of the precision (the same kernel: the
+    digests, compared system by system, say whether a run repeats), and the same
+    sweeps run system by system (solo launches, one after another)."""
     cfgs = inputs.batch_systems(64, seed=0)
     flags = SCHEDULE_FLAGS[args.schedule](P)
     precision = args.precision or "fp32-screen"
@@ -480,8 +481,7 @@ def bench_batch(args, torch, P):
         "events_per_s": ev_s,
         "autotune_trial_ms": trials,
         "other_precision": {"precision": other, "value": value_o, "ms_per_step": ms_o,
-                            "digests_identical": same,
-                            "speedup_of_this_precision": ms_o / ms},
+                            "same_kernel": True, "digests_identical": same},
         "solo_sequential_s": solo_secs,
         "speedup_vs_solo_sequential": solo_secs / (ms * args.steps / 1e3),
     }

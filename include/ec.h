@@ -66,12 +66,10 @@ typedef enum {
 
 typedef enum {
   EC_PREC_FP64 = 0,        /* every candidate distance in FP64                               */
-  EC_PREC_FP32_SCREEN = 1  /* walled cells only.  The same events as EC_PREC_FP64 by
-                              definition (a screen in FP32 with a guard band, FP64 for
-                              the survivors).  On this GPU FP64 runs at the full vector
-                              rate and the plain FP64 search is the faster one at every
-                              size (1M disks 115 against 152 ms a sweep, 16.7M disks
-                              1560 against 2030 ms), so it serves both values */
+  EC_PREC_FP32_SCREEN = 1  /* an alias of EC_PREC_FP64 for walled cells: the same kernel.
+                              (By definition it gives the same events, found with an FP32
+                              screen of the candidates; with FP64 at the full vector rate
+                              no such screen is worth its instructions on this GPU.)       */
 } ec_precision;
 
 typedef enum {
@@ -147,11 +145,11 @@ typedef struct {
   int32_t  dir_mode;        /* ec_dir_mode                                                  */
   int32_t  precision;       /* ec_precision                                                 */
   int32_t  start_mode;      /* ec_start_mode                                                */
-  int32_t  cells_per_block; /* schedule only: simulation cells per workgroup (1, 2, 4);     
+  int32_t  cells_per_block; /* schedule only: simulation cells per workgroup (1, 2, 4);
                                0 = 1 where a colour phase has no more cells than the
                                device has CUs, else 4 when four cells' LDS fits 160 KiB,
                                else 1                                                       */
-  double   screen_margin;   /* guard band of EC_PREC_FP32_SCREEN, in [0, 1e-2]; changes no event */
+  double   screen_margin;   /* in [0, 1e-2]; ignored (EC_PREC_FP32_SCREEN has no screen)    */
   uint64_t seed;            /* Philox4x64-10 key word                                       */
   uint32_t system;          /* index of the system inside a batch (second key-word part)    */
   uint32_t reserved;
@@ -351,8 +349,8 @@ ec_status ec_batch_workspace_bytes(const ec_params* ps, int32_t n_sys, size_t* b
 /* Create the batch in dev_workspace (caller-owned, 256-byte aligned (else
  * EC_E_INVALID), >= ec_batch_workspace_bytes) on hip_stream (borrowed).
  * Each system starts from its lattice as in ec_init_system;
- * ps[i].cells_per_block is ignored (the batch schedule applies, initially
- * 1 in the phase launches).  Synchronises. */
+ * ps[i].cells_per_block is ignored (the batch schedule applies: at first 1, in
+ * the ready queue 4 where as many wavefronts are resident with 4).  Synchronises. */
 ec_status ec_init_batch(const ec_params* ps, int32_t n_sys, void* dev_workspace, size_t ws_bytes,
                         void* hip_stream, ec_batch* out);
 
@@ -369,7 +367,7 @@ ec_status ec_batch_system(ec_batch b, int32_t i, ec_system* out);
  * stream (EC_E_UNSUPPORTED). */
 ec_status ec_batch_set_graph(ec_batch b, int32_t on);
 
-/* Simulation cells per workgroup in the phase launches: 1, 2 or 4
+/* Simulation cells per workgroup in every schedule: 1, 2 or 4
  * (EC_E_UNSUPPORTED if the LDS of that many cells exceeds 160 KiB). */
 ec_status ec_batch_set_cells_per_block(ec_batch b, int32_t cells_per_block);
 
@@ -403,7 +401,8 @@ ec_status ec_destroy_batch(ec_batch b);
  *
  * x[n], y[n]: device arrays, disk-id order, coordinates in [0, L) of a
  * non-overlapping configuration (not checked; ec_set_positions's checks are
- * the caller's to make), advanced in place by sweeps first_sweep ..
+ * the caller's to make: a sweep sees an overlap, error bit 2, only where two
+ * disks come to lie in one bin), advanced in place by sweeps first_sweep ..
  * first_sweep + n_sweeps - 1 of the system p describes (its seed keys the
  * random streams as in ec_init_system, whose first sweep is number 0).
  * digests (may be NULL): device uint64[n_sweeps], the per-sweep event digests

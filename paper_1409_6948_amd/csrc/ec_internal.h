@@ -20,7 +20,7 @@ enum { CNT_LIFTS = 0, CNT_FROZEN = 1, CNT_WALLS = 2, CNT_CHAINS = 3, CNT_PSEUDO 
 // Device error bits.  Any nonzero value also tells every running wave to stop.
 enum {
   ERR_OWN_CAP = 1,     // a cell (own or neighbour) holds more disks than the packing bound
-  ERR_BIN_CAP = 2,     // more than four centres in one LDS bin
+  ERR_BIN_CAP = 2,     // two centres in one LDS bin: disks overlap
   ERR_EVENT_CAP = 4,   // a chain exceeded kMaxEventsPerChain events
   ERR_DRAW_CAP = 8,    // a rejection draw exceeded kMaxDrawTries attempts
   ERR_DEP_WAIT = 16,   // a cell waited longer than dep_wait_ticks for a neighbour of an earlier phase
@@ -97,7 +97,7 @@ struct Status {
 };
 
 // Everything a kernel needs: device pointers into the caller's workspace and
-// the derived constants.  Passed by value.
+// the derived constants.  Kernels read it from device memory.
 struct Dev {
   double* x;                        // [N] positions, disk-id order
   double* y;
@@ -122,7 +122,7 @@ struct Dev {
   int64_t* sweep_ctr;               // [1] number of the current or last sweep, -1 before the first
   double2* psi;                     // [N] per-disk hexatic order Psi_k (re, im)
   double* psi_part;                 // [3 * ceil(N/256)] per-block sums (re, im, neighbours)
-  int32_t* psi_nb;                  // [N] Delaunay neighbour count of each disk
+  int32_t* psi_nb;                  // [N] neighbour count of each disk
   double2* obs_pos;                 // [N] observables: positions grouped by the cells of their grid
   int32_t* obs_id;                  // [N] ids in that order
   int32_t* obs_list;                // [N] sorted places whose Delaunay neighbours need the wide search
@@ -193,8 +193,8 @@ __host__ __device__ inline bool slot_kept(uint32_t meta_word, uint32_t k, double
 }
 
 // LDS of the binned periodic cell: pbins x pbins slots (FP64 position, 32-bit
-// disk id), the slot of every disk, the shuffled start list, one sink slot
-// per lane.
+// disk id), the slot of every disk (16 bits each; the field has 4 n bytes), the
+// shuffled start list, one sink slot per lane.
 struct PeriodicLds {
   int32_t off_pos, off_meta, off_slot_of, off_tmp, off_sink, bytes;
 };

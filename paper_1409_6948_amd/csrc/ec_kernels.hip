@@ -219,7 +219,6 @@ __device__ __forceinline__ int wave_argmin(double s, uint32_t id, bool valid) {
   return wl;
 }
 
-// As wave_argmin, with the minimum of the high words kept in every lane.
 // The argmin in two steps: argmin_key is the lane's key (the high word of s
 // on valid lanes, all ones elsewhere); its wave minimum m is all ones exactly
 // when no lane is valid, since a valid lane's high word (a non-negative
@@ -764,8 +763,8 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 //
 // Costs found by doubling single instructions and by adding idle ones (a
 // wavefront alone on its SIMD): vector and scalar instructions 4 cycles, an LDS
-// store 22 to 34 (by its width, whatever the lanes), an LDS read 8 to 15, and a
-// scalar instruction waits about 16 cycles for any vector instruction that wrote
+// store 22 to 34 (by its width, whatever the lanes), an LDS read 8 to 15, a branch
+// 10 where it is not taken and about 25 where it is, and a scalar instruction waits about 16 cycles for any vector instruction that wrote
 // a scalar register just before, its own operand or not.  So words go to the
 // other lanes by lane reads and records by lane writes, not through LDS; and the
 // lane reads stand together, with vector work or the LDS store between them and
@@ -1020,8 +1019,8 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   EC_W("9:")                                                                                   \
   "s_nop 4"
 // Four copies of the event, of which only the last looks at the limit and takes
-// a branch (14 cycles each time): the loop is entered at the copy from which the
-// limit is reached at the end of the last.
+// a branch: the loop is entered at the copy from which the limit is reached at the
+// end of the last.
 // The code is laid out so that no 8-byte instruction crosses an 8-byte boundary:
 // in a run of such instructions each costs a cycle more where they do.  So 4-byte
 // instructions come in pairs, single ones in their 8-byte encoding (_e64), and
