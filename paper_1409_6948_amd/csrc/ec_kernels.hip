@@ -763,13 +763,14 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 //
 // Costs found by doubling single instructions and by adding idle ones (a
 // wavefront alone on its SIMD): vector and scalar instructions 4 cycles, an LDS
-// store 22 to 34 (by its width, whatever the lanes), an LDS read 8 to 15, a branch
-// 10 where it is not taken and about 25 where it is, and a scalar instruction waits about 16 cycles for any vector instruction that wrote
-// a scalar register just before, its own operand or not.  So words go to the
-// other lanes by lane reads and records by lane writes, not through LDS; and the
-// lane reads stand together, with vector work or the LDS store between them and
-// the next scalar instruction (the contact sum and term stand where they do for
-// that alone: 1M disks 72.4 -> 67.1 ms a sweep).
+// store 22 to 34 (by its width, whatever the lanes), an LDS read 8 to 15, a
+// branch 10 where it is not taken and about 25 where it is, and a scalar
+// instruction waits about 16 cycles for any vector instruction that wrote a
+// scalar register just before, its own operand or not.  So words go to the other
+// lanes by lane reads and records by lane writes, not through LDS; and the lane
+// reads stand together, with vector work or the LDS store between them and the
+// next scalar instruction (the contact sum and term stand where they do for that
+// alone: 1M disks 72.4 -> 67.1 ms a sweep).
 // Measured, ms a sweep: 1M disks 67.1 and 65k disks 60.0, against 84.7 and 72.8
 // with what the winner has to tell sent through LDS and reflections left to the
 // general path, and about 97 and 84 with the loop compiled from C++.
